@@ -74,16 +74,15 @@ struct dflow_ctx {
   const void** dknorm;   // device [n_draft_layers] K-norm gain pointers of the drafter layers
   void* samp;            // sampling decoding partials
   float* samp_row;       // [vocab] logits of the last prompt row (dflow_prefill_sampled)
+  float* rs;             // [mmax] RMSNorm row scales of x (launches of more than SPLIT_MIN_ROWS rows)
   float* kpart;          // K-part partial sums of the split residual and gate/up GEMMs
-  // Matrix-core-order copies of the projections' A operands (the round's
-  // max_batch * block rows, rounded up to 16): x (QKV, gate/up, LM heads),
-  // attention output (O), SwiGLU / relay hidden (down, relay W2), captured
-  // states (W_c), relay input (W1), projected features (drafter context K/V).
-  // Used by the round's calls (frag; prefill reads row-major A); a copy is read
-  // only by the call that wrote it, or -- captured states, features -- by the
-  // next call of the round (accept after verify, commit after accept).
+  // Matrix-core-order copies of the projections' A operands (mmax rows,
+  // rounded up to 16): x (QKV, gate/up, LM heads), attention output (O), SwiGLU
+  // / relay hidden (down, relay W2), captured states (W_c), relay input (W1),
+  // projected features (drafter context K/V).  A copy is read only by the call
+  // that wrote it, or -- captured states, features -- by the next call of the
+  // round (accept after verify, commit after accept).
   void *xf, *attnf, *actf, *hcapf, *uf, *ff;
-  bool frag = false;
 
   // kernel timing record (dflow_profile)
   bool prof = false;
@@ -96,7 +95,7 @@ struct dflow_ctx {
 static const char* kClassName[] = {"gemm.store", "gemm.store_f32", "gemm.resid", "gemm.swiglu",
                                    "gemm.bias_silu", "gemm.bias_f32", "gemm.argmax", "attention"};
 static constexpr int CLS_ATTN = 7;
-// rows of one call (b x B per round, a prefill chunk); up to 128 the weight-streaming GEMM, beyond the tiled one
+// rows of one call (b x B per round, a prefill chunk)
 static constexpr int MAX_ROWS = 1024;
 
 static constexpr int PROF_MAX = 16384;
@@ -203,29 +202,24 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* part_items_out, int* lm_g
   add((size_t)(d->n_draft_layers > 0 ? d->n_draft_layers : 1) * sizeof(void*));   // 23 drafter K-norm gain pointers
   add(samp_workspace_bytes(d->vocab, mmax, d->max_batch));   // 24 sampling partials (log-sum-exp, draw keys)
   add((size_t)d->vocab * 4);                           // 25 fp32 logits of a prompt's last row (sampled prefill)
-  {   // 26 K-part partial sums of the split GEMMs: residual (O, down), gate/up and the range-split projections
+  {   // 26 K-part partial sums of the split GEMMs: residual (O, down), gate/up and the other projections
     const int kt = d->dtype == DFLOW_BF16 ? TT<bf16>::KT : TT<float>::KT;
-    const int po = split_parts(EPI_RESID, d->d / 16, qd / kt), pd = split_parts(EPI_RESID, d->d / 16, d->ffn / kt);
-    const size_t resid = (size_t)(po > pd ? po : pd) * mmax * d->d * 4;
-    const int ps = split_parts(EPI_SWIGLU, 2 * d->ffn / 16, d->d / kt);
-    const size_t rows_split = mmax < SWIGLU_SPLIT_MAX_ROWS ? mmax : SWIGLU_SPLIT_MAX_ROWS;
-    const size_t swiglu = (size_t)ps * rows_split * 2 * d->ffn * 4;
-    size_t need = resid > swiglu ? resid : swiglu;
-    // range split of the narrow plain / fp32 / bias projections: QKV (when in
-    // one part), W_c, drafter context K/V, relay MLP
     const int nc = d->n_draft_layers * 2 * kvd;
-    const int rs_epi[5] = {EPI_STORE_F32, EPI_STORE_F32, EPI_STORE_T, EPI_BIAS_SILU, EPI_BIAS_F32};
-    const int rs_n[5] = {qkvn, d->d, nc, d->relay_hidden, 2 * d->d};
-    const int rs_k[5] = {d->d, d->n_capture * d->d, d->d, 3 * d->d, d->relay_hidden};
-    for (int i = 0; i < 5; ++i) {
+    const int rs_epi[8] = {EPI_RESID, EPI_RESID, EPI_SWIGLU, EPI_STORE_F32, EPI_STORE_F32, EPI_STORE_T, EPI_BIAS_SILU,
+                           EPI_BIAS_F32};
+    const int rs_n[8] = {d->d, d->d, 2 * d->ffn, qkvn, d->d, nc, d->relay_hidden, 2 * d->d};
+    const int rs_k[8] = {qd, d->ffn, d->d, d->d, d->n_capture * d->d, d->d, 3 * d->d, d->relay_hidden};
+    size_t need = 0;
+    for (int i = 0; i < 8; ++i) {
       if (rs_n[i] <= 0 || rs_k[i] <= 0) continue;
-      const size_t r = (size_t)split_parts(rs_epi[i], rs_n[i] / 16, rs_k[i] / kt) * rows_split * rs_n[i] * 4;
+      const size_t rows = rs_epi[i] == EPI_RESID || mmax < split_max_rows(rs_epi[i]) ? mmax : split_max_rows(rs_epi[i]);
+      const size_t r = (size_t)split_parts(rs_epi[i], rs_n[i] / 16, rs_k[i] / kt) * rows * rs_n[i] * 4;
       if (r > need) need = r;
     }
     add(need);
   }
-  {   // 27..32 matrix-core-order operand copies of the round's rows
-    const size_t fr = (size_t)((rows_round + 15) / 16 * 16) * elt;
+  {   // 27..32 matrix-core-order operand copies
+    const size_t fr = (size_t)((mmax + 15) / 16 * 16) * elt;
     add(fr * d->d);                                       // 27 x
     add(fr * qd);                                         // 28 attention output
     add(fr * (d->ffn > d->relay_hidden ? d->ffn : d->relay_hidden));   // 29 SwiGLU / relay hidden
@@ -233,6 +227,7 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* part_items_out, int* lm_g
     add(fr * 3 * d->d);                                   // 31 relay input
     add(fr * d->d);                                       // 32 projected features
   }
+  add((size_t)mmax * 4);                                  // 33 rs: RMSNorm row scales
   L.total = o;
   if (nsplit_out) *nsplit_out = nsplit;
   if (part_items_out) *part_items_out = items;
@@ -342,6 +337,7 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   c->hcapf = b + L.off[30];
   c->uf = b + L.off[31];
   c->ff = b + L.off[32];
+  c->rs = (float*)(b + L.off[33]);
   c->u = c->xn;
   c->hid = c->act;
 
@@ -399,15 +395,13 @@ struct NormIn {            // RMSNorm of the A rows: per-strip sums of squares; 
   const float* ssq = nullptr;
 };
 
-struct Frag {              // matrix-core-order A operand and output copies (skinny launches only)
+struct Frag {              // matrix-core-order A operand and output copies
   const void* a = nullptr;
   FragOut y{}, y2{};
 };
 
-// copy of `cols` columns at c0 of a K-wide consumer operand, when the call uses them
-FragOut fout(const dflow_ctx* c, void* buf, int K, int c0 = 0) {
-  return c->frag ? FragOut{buf, K / c->KT, c0} : FragOut{nullptr, 0, 0};
-}
+// copy of the producer's columns at c0 of a K-wide consumer operand
+FragOut fout(const dflow_ctx* c, void* buf, int K, int c0 = 0) { return FragOut{buf, K / c->KT, c0}; }
 
 hipError_t gemm(dflow_ctx* c, hipStream_t st, int epi, const void* A, int lda, const void* W, int M, int N, int K,
                 void* Y, int ldy, const void* R = nullptr, int ldr = 0, void* Y2 = nullptr, int ldy2 = 0,
@@ -424,8 +418,10 @@ hipError_t gemm(dflow_ctx* c, hipStream_t st, int epi, const void* A, int lda, c
     p.ssq = nin.ssq;
     p.ssq_ld = SSQ_LD;
     p.ssq_parts = c->dm.d / 16;
-    p.eps = c->dm.rms_eps;
+    p.rs = c->rs + (nin.ssq - c->ssq) / SSQ_LD;   // the same rows' scales
   }
+  p.eps = c->dm.rms_eps;
+  p.rs_out = c->rs;
   p.ssq_out = ssq_out;
   p.ssq_out_ld = SSQ_LD;
   p.A = A;
@@ -446,8 +442,7 @@ hipError_t gemm(dflow_ctx* c, hipStream_t st, int epi, const void* A, int lda, c
   p.logits = logits;
   p.ldl = ldl;
   p.col0 = 0;
-  p.part_ws = (epi == EPI_RESID || epi == EPI_SWIGLU || range_split_applies(epi, M, N / 16, ksplit)) ? c->kpart
-                                                                                                    : nullptr;
+  p.part_ws = c->kpart;
   p.cus = c->cus;
   const bool rec = c->prof && c->n_ev < PROF_MAX;
   if (rec) {
@@ -580,19 +575,17 @@ hipError_t decoder_layer(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int
   ffn_n.ssq = c->ssq;
   // QKV projection as fp32 partial sums over qkv_ks K parts (spreads the
   // weight stream evenly over the compute units); its consumers add them
-  // matrix-core-order operands (skinny rounds): x from its producer, the
+  // matrix-core-order operands: x from its producer, the
   // attention output from the combine kernel, the SwiGLU output from gate/up
   Frag fq, fo, fgu, fdn;
-  if (c->frag) {
-    fq.a = c->xf;
-    fo.a = c->attnf;
-    fo.y = fout(c, c->xf, d.d);
-    fgu.a = c->xf;
-    fgu.y = fout(c, c->actf, d.ffn);
-    fdn.a = c->actf;
-    fdn.y = fout(c, c->xf, d.d);
-    fdn.y2 = capf;
-  }
+  fq.a = c->xf;
+  fo.a = c->attnf;
+  fo.y = fout(c, c->xf, d.d);
+  fgu.a = c->xf;
+  fgu.y = fout(c, c->actf, d.ffn);
+  fdn.a = c->actf;
+  fdn.y = fout(c, c->xf, d.d);
+  fdn.y2 = capf;
   if ((e = gemm(c, st, EPI_STORE_F32, c->x, d.d, L.wqkv, M, c->qkv_n, d.d, c->qkv, c->qkv_n, nullptr, 0, nullptr, 0,
                 nullptr, nullptr, 0, attn_n, nullptr, c->qkv_ks, fq)))
     return e;
@@ -643,7 +636,7 @@ hipError_t target_forward(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const 
   NormIn fin;
   fin.ssq = c->ssq + (size_t)lm_row0 * SSQ_LD;
   Frag flm;
-  if (c->frag && lm_row0 == 0) flm.a = c->xf;
+  if (lm_row0 == 0) flm.a = c->xf;
   if ((e = gemm(c, st, EPI_ARGMAX, (char*)c->x + off, d.d, c->w.lm_head, lm_rows, d.vocab, d.d, nullptr, 0, nullptr,
                 0, nullptr, 0, nullptr, logits, d.vocab, fin, nullptr, 1, flm)))
     return e;
@@ -657,7 +650,7 @@ hipError_t project(dflow_ctx* c, hipStream_t st, int M, void* out) {
   hipError_t e;
   const int K = d.n_capture * d.d;
   Frag fr;
-  if (c->frag) fr.a = c->hcapf;
+  fr.a = c->hcapf;
   if ((e = gemm(c, st, EPI_STORE_F32, c->hcap, K, c->w.w_c, M, d.d, K, c->fproj, d.d, nullptr, 0, nullptr, 0,
                 nullptr, nullptr, 0, NormIn(), nullptr, 1, fr)))
     return e;
@@ -676,7 +669,7 @@ hipError_t ctx_append(dflow_ctx* c, hipStream_t st, const void* feat, int nseq, 
   const int ncols = d.n_draft_layers * 2 * c->kv_dim;
   hipError_t e;
   Frag fr;
-  if (c->frag) fr.a = c->ff;
+  fr.a = c->ff;
   if ((e = gemm(c, st, EPI_STORE_T, feat, d.d, c->w.draft_wkv_ctx, M, ncols, d.d, c->ctxkv, ncols, nullptr, 0,
                 nullptr, 0, nullptr, nullptr, 0, NormIn(), nullptr, 1, fr)))
     return e;
@@ -726,7 +719,6 @@ int prefill_impl(dflow_ctx* c, hipStream_t st, int seq, const int32_t* tok, int 
   if ((long long)len + c->dm.block > (long long)c->dm.max_pages * PAGE)
     return fail(DFLOW_ECAPACITY, "prefill: %d tokens exceed the page table (%d)", len, c->dm.max_pages * PAGE);
   c->phase = DFLOW_PHASE_PREFILL;
-  c->frag = false;
   SampleArgs sa;
   if (smp) {
     // counter word 0 of the first draw: the prompt's last position (held in tmp_pos[1])
@@ -740,7 +732,7 @@ int prefill_impl(dflow_ctx* c, hipStream_t st, int seq, const int32_t* tok, int 
     const bool last = p0 + n >= len;
     HIPCHK(launch_set_int(c->tmp_pos, p0, st));
     HIPCHK(launch_embed(c->bf, tok + p0, n, c->w.embed, d.vocab, d.d, c->x, c->status, c->ssq, SSQ_LD,
-                        FragOut{nullptr, 0, 0}, st));
+                        c->rs, d.rms_eps, fout(c, c->xf, d.d), st));
     int* amax = last && !smp ? c->tmp_argmax : nullptr;
     float* lrow = last && smp ? c->samp_row : nullptr;
     HIPCHK(target_forward(c, st, 1, n, c->tmp_pos, pt, amax, lrow, n - 1, 1));
@@ -795,14 +787,11 @@ extern "C" int dflow_draft_block(dflow_ctx* c, hipStream_t st, int nseq, const i
   c->phase = DFLOW_PHASE_DRAFT;
   const dflow_dims& d = c->dm;
   const int B = d.block, M = nseq * B;
-  c->frag = true;
   if (carry_on) {
     Frag f1, f2;
-    if (c->frag) {
-      f1.a = c->uf;
-      f1.y = fout(c, c->actf, d.relay_hidden);
-      f2.a = c->actf;
-    }
+    f1.a = c->uf;
+    f1.y = fout(c, c->actf, d.relay_hidden);
+    f2.a = c->actf;
     HIPCHK(launch_relay_gather(c->bf, 1, c->carry_rec, c->w.embed, c->f, nseq, B, d.d, d.vocab, c->u,
                                fout(c, c->uf, 3 * d.d), st));
     HIPCHK(gemm(c, st, EPI_BIAS_SILU, c->u, 3 * d.d, c->w.relay_w1, M, d.relay_hidden, 3 * d.d, c->hid,
@@ -812,14 +801,14 @@ extern "C" int dflow_draft_block(dflow_ctx* c, hipStream_t st, int nseq, const i
   }
   HIPCHK(launch_relay_input(c->bf, carry_on ? 1 : 0, c->carry_rec, anchor_tok, c->w.embed, c->w.e_mask, c->f, c->bg,
                             c->w.relay_ln_g, c->w.relay_ln_b, d.ln_eps, nseq, B, d.d, d.vocab, c->x, c->status,
-                            c->ssq, SSQ_LD, fout(c, c->xf, d.d), st));
+                            c->ssq, SSQ_LD, c->rs, d.rms_eps, fout(c, c->xf, d.d), st));
   for (int l = 0; l < d.n_draft_layers; ++l)
     HIPCHK(decoder_layer(c, st, c->dlayers[l], nseq, B, anchor_pos, c->c.page_table, pool_layer(c, c->c.ck_pool, l),
                          pool_layer(c, c->c.cv_pool, l), 0, nullptr));
   NormIn fin;
   fin.ssq = c->ssq;
   Frag flm;
-  if (c->frag) flm.a = c->xf;
+  flm.a = c->xf;
   HIPCHK(gemm(c, st, EPI_ARGMAX, c->x, d.d, c->w.draft_lm_head, M, d.vocab, d.d, nullptr, 0, nullptr, 0, nullptr, 0,
               nullptr, draft_logits, d.vocab, fin, nullptr, 1, flm));
   if (!draft_tok && !block_out) return DFLOW_OK;
@@ -836,9 +825,8 @@ extern "C" int dflow_verify_block(dflow_ctx* c, hipStream_t st, int nseq, const 
   c->phase = DFLOW_PHASE_VERIFY;
   const dflow_dims& d = c->dm;
   const int B = d.block, M = nseq * B;
-  c->frag = true;
-  HIPCHK(launch_embed(c->bf, block_tok, M, c->w.embed, d.vocab, d.d, c->x, c->status, c->ssq, SSQ_LD,
-                      fout(c, c->xf, d.d), st));
+  HIPCHK(launch_embed(c->bf, block_tok, M, c->w.embed, d.vocab, d.d, c->x, c->status, c->ssq, SSQ_LD, c->rs,
+                      d.rms_eps, fout(c, c->xf, d.d), st));
   HIPCHK(target_forward(c, st, nseq, B, start_pos, c->c.page_table, tgt_argmax, logits));
   if (hcap)
     HIPCHK(hipMemcpyAsync(hcap, c->hcap, (size_t)M * d.n_capture * d.d * c->elt, hipMemcpyDeviceToDevice, st));
@@ -855,7 +843,6 @@ extern "C" int dflow_accept_and_carry(dflow_ctx* c, hipStream_t st, int nseq, co
   c->phase = DFLOW_PHASE_ACCEPT;
   const dflow_dims& d = c->dm;
   const int B = d.block, M = nseq * B;
-  c->frag = true;
   HIPCHK(launch_accept(block_tok, tgt_argmax, nseq, B, d.carry_window, accept_len, bonus, committed, n_carry,
                        c->carry_rec, st));
   HIPCHK(project(c, st, M, c->f));
@@ -921,7 +908,6 @@ extern "C" int dflow_accept_sampled(dflow_ctx* c, hipStream_t st, int nseq, cons
   if ((rc = sampler_args(c, smp, anchor_pos, &a))) return rc;
   const dflow_dims& d = c->dm;
   const int B = d.block, M = nseq * B;
-  c->frag = true;
   HIPCHK(launch_accept_sampled(logits, draft_logits, block_tok, a, nseq, B, d.carry_window, accept_len, bonus,
                                committed, n_carry, c->carry_rec, c->status, c->samp, st));
   HIPCHK(project(c, st, M, c->f));
@@ -959,7 +945,6 @@ extern "C" int kv_commit(dflow_ctx* c, hipStream_t st, int nseq, const int32_t* 
   if (rc) return rc;
   if (!accept_len || !seq_len) return fail(DFLOW_EINVAL, "kv_commit: null argument");
   c->phase = DFLOW_PHASE_COMMIT;
-  c->frag = true;
   HIPCHK(ctx_append(c, st, c->f, nseq, c->dm.block, seq_len, accept_len, c->c.page_table));
   HIPCHK(launch_commit(accept_len, nseq, seq_len, st));
   return DFLOW_OK;

@@ -214,6 +214,19 @@ __device__ inline float block_sum(float v, float* sh /* >= 32 floats */) {
   return s;
 }
 
+// RMSNorm row scale (sum_c sq[c] / (16 np) + eps)^(-1/2) from a row's per-strip
+// sums of squares in LDS: lane q of the first 16 sums strips c = q (mod 16) in
+// increasing c, then a fixed butterfly -- the order of the weight-streaming
+// kernel's own reduction of the same sums, whatever the launch shape.
+__device__ inline void row_scale_store(const float* sq, int np, float eps, float* out) {
+  if (threadIdx.x >= 16) return;
+  float s = 0.f;
+  for (int c = threadIdx.x; c < np; c += 16) s += sq[c];
+#pragma unroll
+  for (int x = 8; x >= 1; x >>= 1) s += __shfl_xor(s, x, 16);
+  if (threadIdx.x == 0) *out = rsqrtf(s / (float)(np * 16) + eps);
+}
+
 // Device status bits (OR-ed by kernels; read by the host after a sync)
 enum : int {
   ST_BAD_TOKEN = 1,        // token id outside [0, V)

@@ -10,39 +10,45 @@ namespace dflow {
 
 // ---------------------------------------------------------------- embedding
 // Also writes the per-16-column-strip sums of squares of the row (the
-// RMSNorm row scale of the next projection), ssq[row * ssq_ld + c].
+// RMSNorm row scale of the next projection), ssq[row * ssq_ld + c], and that
+// scale itself.
 template <typename T>
 __global__ void embed_kernel(const int* tok, const T* E, int V, int d, T* out, int* status, float* ssq, int ssq_ld,
-                             FragOut of) {
+                             float* rs_out, float eps, FragOut of) {
+  __shared__ float s_sq[SSQ_LD];
   const int row = blockIdx.x;
   int t = tok[row];
   const bool ok = t >= 0 && t < V;
   if (!ok && threadIdx.x == 0) set_status(status, ST_BAD_TOKEN);
   for (int c = threadIdx.x; c < d / 16; c += blockDim.x) {
     float sq = 0.f, vs[16];
+    if (ok) {
+      Row16<T>::load(E + (size_t)t * d + (size_t)c * 16, vs);
+    } else {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const size_t i = (size_t)c * 16 + e;
-      const float v = ok ? TT<T>::ld(E, (size_t)t * d + i) : 0.f;
-      TT<T>::st(out, (size_t)row * d + i, v);
-      vs[e] = v;
-      sq += v * v;
+      for (int e = 0; e < 16; ++e) vs[e] = 0.f;
     }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sq += vs[e] * vs[e];
+    Row16<T>::store(out + (size_t)row * d + (size_t)c * 16, vs);
     frag_st_run<T>(of, row, c * 16, vs, 16);
-    if (ssq) ssq[(size_t)row * ssq_ld + c] = sq;
+    ssq[(size_t)row * ssq_ld + c] = sq;
+    s_sq[c] = sq;
   }
+  __syncthreads();
+  row_scale_store(s_sq, d / 16, eps, rs_out + row);
 }
 
 hipError_t launch_embed(bool isbf, const int* tok, int M, const void* E, int V, int d, void* out, int* status,
-                        float* ssq, int ssq_ld, FragOut of, hipStream_t s) {
+                        float* ssq, int ssq_ld, float* rs_out, float eps, FragOut of, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  if (d % 16) return hipErrorInvalidValue;
+  if (d % 16 || d > 16 * SSQ_LD) return hipErrorInvalidValue;
   if (isbf)
     hipLaunchKernelGGL(embed_kernel<bf16>, dim3(M), dim3(256), 0, s, tok, (const bf16*)E, V, d, (bf16*)out, status,
-                       ssq, ssq_ld, of);
+                       ssq, ssq_ld, rs_out, eps, of);
   else
     hipLaunchKernelGGL(embed_kernel<float>, dim3(M), dim3(256), 0, s, tok, (const float*)E, V, d, (float*)out,
-                       status, ssq, ssq_ld, of);
+                       status, ssq, ssq_ld, rs_out, eps, of);
   return hipGetLastError();
 }
 
@@ -375,7 +381,7 @@ hipError_t launch_relay_gather(bool isbf, int carry_on, const int* carry_rec, co
 }
 
 // x[s*B + 0] = E(anchor); relayed rows: E_mask + beta * LN(h) + gamma; others E_mask.
-// Also writes the per-16-column-strip sums of squares of the stored row.
+// Also writes the per-16-column-strip sums of squares of the stored row and its RMSNorm scale.
 // Thread t owns the 16-column chunks t, t + 256, ... (d <= 16 * 256 * RC);
 // the carried state is read once and kept in registers for both LayerNorm passes.
 template <typename T>
@@ -383,9 +389,10 @@ __global__ void __launch_bounds__(256) relay_input_kernel(int carry_on, const in
                                                           const T* e_mask, const T* f,
                                                           const float* bg, const T* ln_g, const T* ln_b, float ln_eps,
                                                           int B, int d, int V, T* x, int* status, float* ssq,
-                                                          int ssq_ld, FragOut of) {
+                                                          int ssq_ld, float* rs_out, float rms_eps, FragOut of) {
   constexpr int RC = 2;
   __shared__ float sh[32];
+  __shared__ float s_sq[SSQ_LD];
   const int row = blockIdx.x;
   const int s = row / B, i = row - s * B;
   const int nc = d / 16;
@@ -467,23 +474,26 @@ __global__ void __launch_bounds__(256) relay_input_kernel(int carry_on, const in
     float sq = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) sq += v[e] * v[e];
-    if (ssq) ssq[(size_t)row * ssq_ld + c] = sq;
+    ssq[(size_t)row * ssq_ld + c] = sq;
+    s_sq[c] = sq;
   }
+  __syncthreads();
+  row_scale_store(s_sq, nc, rms_eps, rs_out + row);
 }
 
 hipError_t launch_relay_input(bool isbf, int carry_on, const int* carry_rec, const int* anchor, const void* E,
                               const void* e_mask, const void* f, const float* bg, const void* ln_g,
                               const void* ln_b, float ln_eps, int nseq, int B, int d, int V, void* x, int* status,
-                              float* ssq, int ssq_ld, FragOut of, hipStream_t s) {
+                              float* ssq, int ssq_ld, float* rs_out, float rms_eps, FragOut of, hipStream_t s) {
   if (d % 16 || d > 16 * 256 * 2) return hipErrorInvalidValue;
   if (isbf)
     hipLaunchKernelGGL(relay_input_kernel<bf16>, dim3(nseq * B), dim3(256), 0, s, carry_on, carry_rec, anchor,
                        (const bf16*)E, (const bf16*)e_mask, (const bf16*)f, bg, (const bf16*)ln_g,
-                       (const bf16*)ln_b, ln_eps, B, d, V, (bf16*)x, status, ssq, ssq_ld, of);
+                       (const bf16*)ln_b, ln_eps, B, d, V, (bf16*)x, status, ssq, ssq_ld, rs_out, rms_eps, of);
   else
     hipLaunchKernelGGL(relay_input_kernel<float>, dim3(nseq * B), dim3(256), 0, s, carry_on, carry_rec, anchor,
                        (const float*)E, (const float*)e_mask, (const float*)f, bg, (const float*)ln_g,
-                       (const float*)ln_b, ln_eps, B, d, V, (float*)x, status, ssq, ssq_ld, of);
+                       (const float*)ln_b, ln_eps, B, d, V, (float*)x, status, ssq, ssq_ld, rs_out, rms_eps, of);
   return hipGetLastError();
 }
 

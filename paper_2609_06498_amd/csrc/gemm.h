@@ -44,16 +44,16 @@ struct GemmParams {
   int norm;
   const float* ssq; int ssq_ld; int ssq_parts;
   float eps;
+  const float* rs;   // [M] the row scales themselves, for launches of more than SPLIT_MIN_ROWS rows
   // EPI_RESID: per-16-column-strip sums of squares of the stored rows, [m * ssq_out_ld + strip]
   float* ssq_out; int ssq_out_ld;
   // EPI_STORE_F32 only: K split into ksplit parts; part h writes its partial
   // sums at Y + h * y_part (floats), and the consumer adds the parts
   int ksplit; size_t y_part;
-  // EPI_RESID above SPLIT_MIN_ROWS rows, EPI_SWIGLU from SPLIT_MIN_ROWS + 1
-  // to SWIGLU_SPLIT_MAX_ROWS rows: fp32 scratch of split_parts(epi, ntiles,
-  // ktiles) x M x N floats for the K-part partial sums; the narrow plain,
-  // fp32 and bias projections under range_split_applies the same (null: no
-  // split)
+  float* rs_out;     // EPI_RESID above SPLIT_MIN_ROWS rows: [M] RMSNorm scales of the stored rows (for d = N)
+  // above SPLIT_MIN_ROWS rows: fp32 scratch of split_parts(epi, ntiles,
+  // ktiles) x M x N floats for K-part partial sums (EPI_RESID always; the
+  // others up to split_max_rows(epi) rows; null: no split)
   float* part_ws;
   int cus;                          // compute units (0: unknown, no balance-driven split)
   // A read from its matrix-core-order copy (afrag_off; null: from A), and
@@ -63,19 +63,18 @@ struct GemmParams {
   FragOut yf, y2f;
 };
 
-constexpr int SPLIT_MIN_ROWS = 48, SWIGLU_SPLIT_MAX_ROWS = 256;
+// Up to SPLIT_MIN_ROWS rows the weight-streaming kernel; more rows the tiled one.
+constexpr int SPLIT_MIN_ROWS = 48;
+// Most rows at which a launch may be split into K-part partial sums (beyond,
+// the tiles alone fill the compute units, and the scratch would only grow).
+inline int split_max_rows(int epi) { return epi == EPI_SWIGLU ? 256 : 512; }
 
 struct GemmShape { int ng; int waves; int groups; };
 GemmShape gemm_shape(int ntiles, int ktiles, int epi, int ksplit = 1);
 int gemm_ksplit(int ntiles, int ktiles, int cus);
-// K parts of a split residual or SwiGLU GEMM (the weight-streaming kernel's
-// wave count for (N, K), so every part is one of its K ranges)
+// K parts of a split launch (the weight-streaming kernel's wave count for
+// (N, K), so every part is one of its K ranges)
 int split_parts(int epi, int ntiles, int ktiles);
-// Whether a plain, fp32, bias + SiLU or bias projection (no K parts) of M rows
-// takes the range split: SPLIT_MIN_ROWS < M <= SWIGLU_SPLIT_MAX_ROWS and a
-// weight too narrow for the tiled kernel's workgroup count; it needs
-// split_parts(epi, ntiles, ktiles) x M x N floats of part_ws
-bool range_split_applies(int epi, int M, int ntiles, int ksplit);
 hipError_t launch_gemm(bool bf16, int epi, const GemmParams& p, hipStream_t s);
 hipError_t launch_pack(bool bf16, const void* w, int N, int K, int gate_up, const void* col_gain, void* out,
                        hipStream_t s);

@@ -8,10 +8,12 @@
 // ranges that depend only on (N, K), and the wave partials are summed in LDS
 // in wave order.  Every output element therefore sees the same reduction
 // order whatever M is, which keeps results batch- and position-invariant.
+// Up to SPLIT_MIN_ROWS rows; more rows go to the tiled kernel (gemm_tile.h).
 #include <cmath>
 
 #include "common.h"
 #include "gemm.h"
+#include "gemm_tile.h"
 
 namespace dflow {
 
@@ -360,311 +362,66 @@ __global__ void __launch_bounds__(512) gemm_kernel(GemmParams p) {
 }
 
 // ------------------------------------------------------------------ large M
-// Tiled GEMM for M > 128 rows (serving batches, prefill chunks): A and W
-// staged through LDS in MFMA fragment order.  The K loop runs the same contiguous ranges as the weight-
-// streaming kernel's waves (gemm_shape's wave count for this N, K) and folds
-// each range's MFMA chain into the running sum in range order, starting from
-// zero, so every output element is bit-identical to what the weight-streaming
-// kernel computes for it at any M: the result of a row never depends on the
-// batch it is part of.  The M tiles of one strip tile are dispatched to the
-// same XCD (round-robin placement, id mod 8), so its weights are fetched from
-// HBM once and shared through that XCD's L2.
-// Same row scale as the weight-streaming kernel: lane q of a 16-lane group
-// sums strips c = q (mod 16) in increasing c, then the fixed butterfly.
-__device__ inline float norm_row_scale(const GemmParams& p, int m, int q16) {
-  constexpr int EL = 16;
-  const int np = p.ssq_parts;
-  gf32* r = (gf32*)(p.ssq) + (size_t)m * p.ssq_ld + q16;
-  float v[EL];
-#pragma unroll
-  for (int it = 0; it < EL; ++it) v[it] = r[16 * it];   // padded rows: ssq_ld >= 256 entries
-  float sa = 0.f;
-#pragma unroll
-  for (int it = 0; it < EL; ++it) sa += (q16 + 16 * it < np) ? v[it] : 0.f;
-  for (int c = q16 + 16 * EL; c < np; c += 16) sa += p.ssq[(size_t)m * p.ssq_ld + c];
-#pragma unroll
-  for (int x = 8; x >= 1; x >>= 1) sa += __shfl_xor(sa, x, 16);
-  return rsqrtf(sa / (float)(np * 16) + p.eps);
+// Tile shapes of the many-row GEMM, and a launch's time by how the workgroups
+// fall on the compute units.  Measured on the Qwen3 projections (8 x 64 .. 64 x
+// 200 k tiles per workgroup, bf16): a workgroup's k tile takes t1 us when it has
+// its compute unit to itself and tn when the unit holds several.  The widest
+// tile reaches 1.17 PFLOP/s on full launches (8B gate/up at 1024 rows 176 us,
+// the register-staged 128 x 128 tile before it 245); the smaller ones are for
+// row counts and widths that would leave units idle (8B QKV at 128 rows 18.6 us
+// at 128 x 128, 15.5 at 128 x 64; 1.7B gate/up at 300 rows 29.7 us at 128 x
+// 128, 23.2 at 64 x 128).
+typedef TileShape<2, 4, 4, 2, 1, 2> Tile128x128;
+typedef TileShape<2, 2, 4, 2, 1, 3> Tile128x64;
+typedef TileShape<1, 4, 4, 2, 1, 3> Tile64x128;
+typedef TileShape<2, 2, 2, 2, 1, 4> Tile64x64;
+struct TileCost { int bm, bs; double t1, tn; };
+constexpr TileCost TILES[] = {{128, 8, 0.23, 0.23}, {128, 4, 0.18, 0.148}, {64, 8, 0.19, 0.146}, {64, 4, 0.15, 0.10}};
+constexpr int N_TILES = sizeof(TILES) / sizeof(TILES[0]);
+
+// the fastest tile for M rows x ntiles strips x ktiles in ks K parts, and its time in us
+static int pick_tile(int M, int ntiles, int ktiles, int ks, int cus, double* us) {
+  int best = 0;
+  double tb = 1e30;
+  for (int i = 0; i < N_TILES; ++i) {
+    const TileCost& c = TILES[i];
+    const long long wgs = (long long)((M + c.bm - 1) / c.bm) * ((ntiles + c.bs - 1) / c.bs) * ks;
+    const long long n = (wgs + cus - 1) / cus;
+    const double t = (double)n * ((ktiles + ks - 1) / ks) * (n == 1 ? c.t1 : c.tn);
+    if (t < tb) {
+      tb = t;
+      best = i;
+    }
+  }
+  *us = tb;
+  return best;
 }
 
-constexpr int TILE_BM = 128, TILE_BS = 8, TILE_CW = TILE_BS * 16 + 4;
-constexpr size_t TILE_LDS = (size_t)TILE_BM * TILE_CW * sizeof(float);   // C tile (widest); >= 2 staging buffers
-
-// Workgroup tile 128 rows x BS strips (BS = 8: 128 columns; 4 for narrow
-// weights, so that enough workgroups exist), four waves of 64 rows x BS/2
-// strips.  Per k tile the workgroup stages 8 KB of A and BS KB of W; loads
-// run TILE_D - 1 k tiles ahead in registers and the LDS is double buffered.
-// About 250 registers per lane and at most 68 KB of LDS, so two workgroups
-// share a compute unit.
-constexpr int TILE_D = 4;
-// NTW: the weight tiles are loaded non-temporally (a launch with one M tile
-// reads each weight byte once; with several, the M tiles of a strip tile share
-// it through L2 and the loads stay temporal).
-template <typename T, int EPI, bool NORM, int BS, bool NTW>
-__global__ void __launch_bounds__(256, 2) gemm_tile_kernel(GemmParams p, int nw, int mt, int units) {
-  constexpr int KL = TT<T>::KL;
-  constexpr int KT = TT<T>::KT;
-  constexpr int D = TILE_D;
-  constexpr int WS = BS / 2;                  // strips per wave
-  constexpr int NWC = BS / 4;                 // W chunks per thread and k tile
-  constexpr int CW = BS * 16 + 4;             // padded C-tile row
-  extern __shared__ float lds[];
-  __shared__ float s_rs[NORM ? TILE_BM : 1];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = w >> 1, wn = w & 1;
-  // block -> (m tile, unit = strip tile x K part); the m tiles of a unit share an XCD
-  const int x8 = blockIdx.x & 7, y = blockIdx.x >> 3;
-  const int mtile = y % mt, unit = (y / mt) * 8 + x8;
-  if (unit >= units) return;                                  // padding of the dispatch grid
-  const int ks = p.ksplit > 1 ? p.ksplit : 1;
-  const int stile = unit / ks, h = unit - stile * ks;
-  const int nt0 = stile * BS;
-  const int nvalid = min(BS, p.ntiles - nt0);
-  const int m0 = mtile * TILE_BM;
-  const int rows = min(TILE_BM, p.M - m0);
-  const int kpart = (p.ktiles + ks - 1) / ks;
-  const int k0 = min(p.ktiles, h * kpart), k1 = min(p.ktiles, k0 + kpart);
-  const int kper = (k1 - k0 + nw - 1) / nw;                  // the weight-streaming kernel's wave ranges
-  const T* Ap = reinterpret_cast<const T*>(p.A);
-  const gu4* Wp = (const gu4*)(p.W);
-
-  if constexpr (NORM) {
-    const int q16 = threadIdx.x & 15, grp = threadIdx.x >> 4;   // 16 groups of 16 lanes
-    for (int r = grp; r < TILE_BM; r += 16) {
-      const float rs = norm_row_scale(p, m0 + min(r, rows - 1), q16);
-      if (q16 == 0) s_rs[r] = rs;
-    }
-  }
-
-  // staging: A chunk c (row c/4, quarter c%4 of its KT values) goes to the
-  // fragment slot of its m tile, XOR-swizzled within the quarter's 16 slots
-  // (slot q*16 + (r ^ 2q)) so that the eight lanes of one 16-byte LDS write
-  // pass (two rows x four quarters) hit distinct banks; the reader undoes the
-  // swizzle.  W chunk c is lane c%64 of strip c/64.
-  u32x4_t* sa = reinterpret_cast<u32x4_t*>(lds);             // [buffer][8 m tiles][64]
-  u32x4_t* sw = sa + 2 * 512;                                 // [buffer][BS strips][64]
-  // From the matrix-core-order copy (p.Af) chunk c is lane c%64 of the 1 KB
-  // tile of m tile c/64: contiguous loads and LDS slots, no swizzle needed
-  // (rows past M in the last 16-row tile are loaded and never stored).
-  const bool af = p.Af != nullptr;
-  const gu4* asrc[2];
-  const gu4* wsrc[NWC];
-  int adst[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int c = threadIdx.x + 256 * i;
-    if (af) {
-      const int mtg = min(m0 / 16 + (c >> 6), (p.M + 15) / 16 - 1);
-      asrc[i] = (const gu4*)(p.Af) + (size_t)mtg * p.ktiles * 64 + (c & 63);
-      adst[i] = c;
-    } else {
-      const int r = c >> 2, q = c & 3;
-      asrc[i] = (const gu4*)(Ap + (size_t)(m0 + min(r, rows - 1)) * p.lda + q * KL);   // clamped rows are not stored
-      adst[i] = (r >> 4) * 64 + q * 16 + ((r & 15) ^ (2 * q));
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < NWC; ++i) {
-    const int c = threadIdx.x + 256 * i;
-    wsrc[i] = Wp + (size_t)min(nt0 + (c >> 6), p.ntiles - 1) * p.ktiles * 64 + (c & 63);   // clamped strips: not stored
-  }
-  constexpr int AST = KT * (int)sizeof(T) / 16;              // 16-byte chunks per k tile along an A row
-  const int ast = af ? 64 : AST;
-  u32x4_t ra[D][2], rw[D][NWC];                               // register slots
-  auto load = [&](int slot, int kt) {                         // clamped: a load past the end is never used
-    kt = min(kt, k1 - 1);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) ra[slot][i] = asrc[i][(size_t)kt * ast];
-#pragma unroll
-    for (int i = 0; i < NWC; ++i)
-      rw[slot][i] = NTW ? __builtin_nontemporal_load(&wsrc[i][(size_t)kt * 64]) : wsrc[i][(size_t)kt * 64];
-  };
-  auto store = [&](int slot, int buf) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) sa[buf * 512 + adst[i]] = ra[slot][i];
-#pragma unroll
-    for (int i = 0; i < NWC; ++i) sw[buf * BS * 64 + threadIdx.x + 256 * i] = rw[slot][i];
-  };
-
-  f32x4_t acc[4][WS], tot[4][WS];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < WS; ++j) acc[i][j] = tot[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  int folds = 0;
-  auto fold = [&]() {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < WS; ++j) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) tot[i][j][r] += acc[i][j][r];
-        acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      }
-    ++folds;
-  };
-  auto compute = [&](int buf) {
-    u32x4_t a[4], b[WS];
-    const int aslot = af ? lane : (lane & 48) | ((lane & 15) ^ (2 * (lane >> 4)));   // fragment lane -> slot
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = sa[buf * 512 + (wm * 4 + i) * 64 + aslot];
-#pragma unroll
-    for (int j = 0; j < WS; ++j) b[j] = sw[buf * BS * 64 + (wn * WS + j) * 64 + lane];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < WS; ++j) acc[i][j] = mma_frag(T(), a[i], b[j], acc[i][j]);
-  };
-  // k tile t sits in LDS buffer (t - k0) & 1 and, before that, in register
-  // slot (t - k0) % D; step t stores t + 1, loads t + D, multiplies t
-  auto step = [&](int t, int j) {
-    store((j + 1) % D, ((t - k0) & 1) ^ 1);
-    load(j, t + D);
-    compute((t - k0) & 1);
-    if ((t - k0 + 1) % kper == 0 || t + 1 == k1) fold();     // end of a range
-    __syncthreads();
-  };
-
-  if (k0 < k1) {
-#pragma unroll
-    for (int j = 0; j < D; ++j) load(j, k0 + j);
-    store(0, 0);
-  }
-  __syncthreads();
-  int kt = k0;
-  for (; kt + D <= k1; kt += D) {                             // uniform
-#pragma unroll
-    for (int j = 0; j < D; ++j) step(kt + j, j);
-  }
-#pragma unroll
-  for (int j = 0; j < D; ++j)                                 // the last k1 - kt < D tiles
-    if (kt + j < k1) step(kt + j, j);
-  while (folds < nw) fold();                                  // empty ranges add +0, as their waves do
-  __syncthreads();                                            // staging buffers free for the C tile
-
-  // C tile to LDS (the staging buffers are free), then the epilogue
-  float* ct = lds;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < WS; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        ct[(wm * 64 + i * 16 + 4 * (lane >> 4) + r) * CW + (wn * WS + j) * 16 + (lane & 15)] = tot[i][j][r];
-  __syncthreads();
-  const int ncols = nvalid * 16;
-  const int colbase = p.col0 + nt0 * 16;
-  if constexpr (EPI == EPI_ARGMAX) {
-    for (int e = threadIdx.x; e < rows * ncols; e += blockDim.x) {
-      const int m = e / ncols, n = e - m * ncols;
-      float v = ct[m * CW + n];
-      if constexpr (NORM) ct[m * CW + n] = v = v * s_rs[m];
-      if (p.logits) p.logits[(size_t)(m0 + m) * p.ldl + colbase + n] = v;
-    }
-    __syncthreads();
-    // one key per row and group of two strips, as the weight-streaming kernel's workgroups
-    const int ngrp = (nvalid + 1) / 2;
-    for (int e = threadIdx.x; e < rows * ngrp; e += blockDim.x) {
-      const int m = e / ngrp, gi = e - m * ngrp;
-      const int c0 = gi * 32, c1 = min(ncols, c0 + 32);
-      float best = ct[m * CW + c0];
-      int bi = c0;
-      for (int n = c0 + 1; n < c1; ++n) {
-        const float v = ct[m * CW + n];
-        if (v > best) { best = v; bi = n; }
-      }
-      p.amax[(size_t)(nt0 / 2 + gi) * p.amax_ld + m0 + m] = argmax_key(best, colbase + bi);
-    }
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    const int half = ncols / 2;
-    const int obase = (p.col0 + nt0 * 16) / 2;
-    for (int e = threadIdx.x; e < rows * half; e += blockDim.x) {
-      const int m = e / half, c = e - m * half;
-      const int strip = c >> 3, cc = c & 7;
-      float gt = ct[m * CW + strip * 16 + cc];
-      float up = ct[m * CW + strip * 16 + 8 + cc];
-      if constexpr (NORM) {
-        gt *= s_rs[m];
-        up *= s_rs[m];
-      }
-      const float y = silu(gt) * up;
-      TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)(m0 + m) * p.ldy + obase + c, y);
-      frag_st<T>(p.yf, m0 + m, obase + c, y);
-    }
-  } else {
-    for (int e = threadIdx.x; e < rows * ncols; e += blockDim.x) {
-      const int m = e / ncols, n = e - m * ncols;
-      const int col = colbase + n;
-      const size_t gm = (size_t)(m0 + m);
-      float v = ct[m * CW + n];
-      if constexpr (NORM) v *= s_rs[m];
-      if constexpr (EPI == EPI_STORE_T) {
-        TT<T>::st(reinterpret_cast<T*>(p.Y), gm * p.ldy + col, v);
-      } else if constexpr (EPI == EPI_STORE_F32) {
-        reinterpret_cast<float*>(p.Y)[(size_t)h * p.y_part + gm * p.ldy + col] = v;
-      } else if constexpr (EPI == EPI_RESID) {
-        v = TT<T>::rnd(v + TT<T>::ld(reinterpret_cast<const T*>(p.R), gm * p.ldr + col));
-        TT<T>::st(reinterpret_cast<T*>(p.Y), gm * p.ldy + col, v);
-        if (p.Y2) TT<T>::st(reinterpret_cast<T*>(p.Y2), gm * p.ldy2 + col, v);
-        frag_st<T>(p.yf, (int)gm, col, v);
-        frag_st<T>(p.y2f, (int)gm, col, v);
-        ct[m * CW + n] = v;
-      } else if constexpr (EPI == EPI_BIAS_SILU) {
-        v += TT<T>::ld(reinterpret_cast<const T*>(p.bias), col);
-        TT<T>::st(reinterpret_cast<T*>(p.Y), gm * p.ldy + col, silu(v));
-        frag_st<T>(p.yf, (int)gm, col, silu(v));
-      } else if constexpr (EPI == EPI_BIAS_F32) {
-        v += TT<T>::ld(reinterpret_cast<const T*>(p.bias), col);
-        reinterpret_cast<float*>(p.Y)[gm * p.ldy + col] = v;
-      }
-    }
-    if constexpr (EPI == EPI_RESID) {
-      if (p.ssq_out) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < rows * nvalid; e += blockDim.x) {
-          const int m = e / nvalid, j = e - m * nvalid;
-          float sq = 0.f;
-#pragma unroll
-          for (int c = 0; c < 16; ++c) {
-            const float v = ct[m * CW + j * 16 + c];
-            sq += v * v;
-          }
-          p.ssq_out[(size_t)(m0 + m) * p.ssq_out_ld + nt0 + j] = sq;
-        }
-      }
-    }
-  }
-}
-
-template <typename T, int EPI, bool NORM, int BS, bool NTW>
-static hipError_t launch_tile_bs(const GemmParams& p, const GemmShape& sh, int ks, int mt, hipStream_t st) {
-  const int units = (p.ntiles + BS - 1) / BS * ks;
+template <typename T, int EPI, typename S>
+static hipError_t launch_tile_shape(const GemmParams& p, int waves, int ks, hipStream_t st) {
+  const int mt = (p.M + S::BM - 1) / S::BM, units = (p.ntiles + S::BS - 1) / S::BS * ks;
   const int blocks = (units + 7) / 8 * 8 * mt;
-  // the C tile needs more than the default dynamic LDS; set once per
+  // the ring needs more than the default dynamic LDS; set once per
   // instantiation (thread-safe static initialisation)
-  static const hipError_t attr = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&gemm_tile_kernel<T, EPI, NORM, BS, NTW>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, (int)TILE_LDS);
+  constexpr size_t lds = S::STAGE * S::NS;
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_tile_kernel<T, EPI, S>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (attr != hipSuccess) return attr;
-  const size_t lds = (size_t)TILE_BM * (BS * 16 + 4) * sizeof(float);
-  hipLaunchKernelGGL((gemm_tile_kernel<T, EPI, NORM, BS, NTW>), dim3(blocks), dim3(256), lds, st, p, sh.waves, mt,
-                     units);
+  hipLaunchKernelGGL((gemm_tile_kernel<T, EPI, S>), dim3(blocks), dim3(S::NW * 64), lds, st, p, waves, mt, units);
   return hipGetLastError();
 }
 
-// Tile width from (N, M): 8 strips unless that leaves fewer workgroups than
-// compute units.  The arithmetic of an output element does not depend on it.
-template <typename T, int EPI, bool NORM>
-static hipError_t launch_tile(const GemmParams& p, const GemmShape& sh, int ks, hipStream_t st) {
-  const int mt = (p.M + TILE_BM - 1) / TILE_BM;
-  const int wide = (p.ntiles + TILE_BS - 1) / TILE_BS * ks * mt;
-  if (mt == 1) {
-    if (wide < 256) return launch_tile_bs<T, EPI, NORM, 4, true>(p, sh, ks, mt, st);
-    return launch_tile_bs<T, EPI, NORM, 8, true>(p, sh, ks, mt, st);
+// K parts each folding `waves` ranges; the arithmetic of an output element does not depend on the tile.
+template <typename T, int EPI>
+static hipError_t launch_tile(const GemmParams& p, int waves, int ks, hipStream_t st) {
+  if (!p.Af || (p.norm && !p.rs)) return hipErrorInvalidValue;
+  double us;
+  switch (pick_tile(p.M, p.ntiles, p.ktiles, ks, p.cus > 0 ? p.cus : 256, &us)) {
+    case 0: return launch_tile_shape<T, EPI, Tile128x128>(p, waves, ks, st);
+    case 1: return launch_tile_shape<T, EPI, Tile128x64>(p, waves, ks, st);
+    case 2: return launch_tile_shape<T, EPI, Tile64x128>(p, waves, ks, st);
   }
-  if (wide < 256) return launch_tile_bs<T, EPI, NORM, 4, false>(p, sh, ks, mt, st);
-  return launch_tile_bs<T, EPI, NORM, 8, false>(p, sh, ks, mt, st);
+  return launch_tile_shape<T, EPI, Tile64x64>(p, waves, ks, st);
 }
 
 // Launch shape from (N, K) (and the K parts) only, never from M.  Wide weights (>= 1024
@@ -709,16 +466,9 @@ static hipError_t launch_mtn(const GemmParams& p, const GemmShape& sh, hipStream
     hipLaunchKernelGGL(kern, dim3(sh.groups), dim3(sh.waves * 64), lds, st, p);
     return hipGetLastError();
   };
-  // the tiled kernel for more than 128 rows, and from 64 rows for weights wide
-  // enough to give it a workgroup per compute unit or so (measured crossover:
-  // the weight-streaming kernel re-reads A from L2 once per strip group)
-  const int ks = p.ksplit > 1 ? p.ksplit : 1;
-  const bool tile = mt > 8 || (mt >= 4 && (p.ntiles + TILE_BS - 1) / TILE_BS * ks >= 96);
-  if (tile) return launch_tile<T, EPI, NORM>(p, sh, ks, st);
   if (mt <= 1) return go(gemm_kernel<T, NG, 1, EPI, NORM>, 1);
   if (mt <= 2) return go(gemm_kernel<T, NG, 2, EPI, NORM>, 2);
-  if (mt <= 4) return go(gemm_kernel<T, NG, 4, EPI, NORM>, 4);
-  return go(gemm_kernel<T, NG, 8, EPI, NORM>, 8);
+  return go(gemm_kernel<T, NG, 4, EPI, NORM>, 4);
 }
 
 // The RMSNorm row scale is instantiated only for the projections that follow a norm.
@@ -741,13 +491,11 @@ static hipError_t launch_ng(const GemmParams& p, const GemmShape& sh, hipStream_
   return sh.ng == 2 ? launch_mt<T, 2, EPI>(p, sh, st) : launch_mt<T, 1, EPI>(p, sh, st);
 }
 
-// Residual epilogue of the K-split path: one thread per (row, 16-column
-// strip) adds the fp32 parts in part order from +0 -- the order in which the
-// weight-streaming kernel adds its waves' ranges, so each row is bit-identical
-// to that kernel's -- then applies its EPI_RESID epilogue: rnd(sum + R) to Y
-// (and Y2) and the strip's sum of squares of the stored values.
+// ---- K-part folds (launches of more than SPLIT_MIN_ROWS rows)
 // The KS parts (KS > 0: all loads in flight at once; KS = 0: a loop over ks)
-// of a thread's 16 columns, summed in part order from +0.
+// of a thread's 16 columns, summed in part order from +0 -- the order in which
+// the weight-streaming kernel adds its waves' ranges, so each row is
+// bit-identical to that kernel's.
 template <int KS>
 __device__ inline void sum_parts16(const float* part, size_t part_stride, int ks, size_t off, float (&s)[16]) {
 #pragma unroll
@@ -770,153 +518,74 @@ __device__ inline void sum_parts16(const float* part, size_t part_stride, int ks
   }
 }
 
+// Residual epilogue: one workgroup per row, a thread per 16-column strip:
+// rnd(sum + R) to Y (and Y2), the strip's sum of squares of the stored values
+// and, from those in LDS, the row's RMSNorm scale for the next projection.
 template <typename T, int KS>
-__global__ void __launch_bounds__(256) resid_reduce_kernel(const float* part, size_t part_stride, int ks, int M,
-                                                           int N, const T* R, int ldr, T* Y, int ldy, T* Y2, int ldy2,
-                                                           float* ssq_out, int ssq_ld, int strip0, FragOut yf,
-                                                           FragOut y2f) {
+__global__ void __launch_bounds__(256) resid_reduce_kernel(const float* part, size_t part_stride, int ks, int N,
+                                                           const T* R, int ldr, T* Y, int ldy, T* Y2, int ldy2,
+                                                           float* ssq_out, int ssq_ld, float* rs_out, float eps,
+                                                           FragOut yf, FragOut y2f) {
+  __shared__ float s_sq[SSQ_LD];
   const int nstrips = N / 16;
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= M * nstrips) return;
-  const int m = e / nstrips, j = e - m * nstrips;
-  float r[16], s[16];
-  Row16<T>::load(R + (size_t)m * ldr + j * 16, r);
-  sum_parts16<KS>(part, part_stride, ks, (size_t)m * N + j * 16, s);
-  float sq = 0.f;
+  const int m = blockIdx.x;
+  for (int j = threadIdx.x; j < nstrips; j += blockDim.x) {
+    float r[16], s[16];
+    Row16<T>::load(R + (size_t)m * ldr + j * 16, r);
+    sum_parts16<KS>(part, part_stride, ks, (size_t)m * N + j * 16, s);
+    float sq = 0.f;
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    s[c] = TT<T>::rnd(s[c] + r[c]);
-    sq += s[c] * s[c];
+    for (int c = 0; c < 16; ++c) {
+      s[c] = TT<T>::rnd(s[c] + r[c]);
+      sq += s[c] * s[c];
+    }
+    Row16<T>::store(Y + (size_t)m * ldy + j * 16, s);
+    if (Y2) Row16<T>::store(Y2 + (size_t)m * ldy2 + j * 16, s);
+    frag_st_run<T>(yf, m, j * 16, s, 16);
+    frag_st_run<T>(y2f, m, j * 16, s, 16);
+    ssq_out[(size_t)m * ssq_ld + j] = sq;
+    s_sq[j] = sq;
   }
-  Row16<T>::store(Y + (size_t)m * ldy + j * 16, s);
-  if (Y2) Row16<T>::store(Y2 + (size_t)m * ldy2 + j * 16, s);
-  frag_st_run<T>(yf, m, j * 16, s, 16);
-  frag_st_run<T>(y2f, m, j * 16, s, 16);
-  if (ssq_out) ssq_out[(size_t)m * ssq_ld + strip0 + j] = sq;
+  __syncthreads();
+  row_scale_store(s_sq, nstrips, eps, rs_out + m);
 }
 
 int split_parts(int epi, int ntiles, int ktiles) { return gemm_shape(ntiles, ktiles, epi, 1).waves; }
 
-// SwiGLU epilogue of the K-split path: one thread per (row, 16-column strip of
-// 8 gate + 8 up columns), parts added in part order from +0, then the
-// weight-streaming kernel's epilogue (row scale, silu(gate) * up, rounding).
-// Every 16-lane group computes the row scale (the same value) before any lane
-// leaves.
-template <typename T, bool NORM, int KS>
+// SwiGLU epilogue: one thread per (row, 16-column strip of 8 gate + 8 up
+// columns), then the weight-streaming kernel's epilogue (row scale,
+// silu(gate) * up, rounding).
+template <typename T, int KS>
 __global__ void __launch_bounds__(256) swiglu_reduce_kernel(GemmParams p, const float* part, size_t part_stride,
                                                             int ks, int N) {
   const int m = blockIdx.y;
-  float rs = 1.f;
-  if constexpr (NORM) rs = norm_row_scale(p, m, threadIdx.x & 15);
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= N / 16) return;
+  const float rs = p.norm ? p.rs[m] : 1.f;
   float s[16];
   sum_parts16<KS>(part, part_stride, ks, (size_t)m * N + j * 16, s);
   float y[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
     float gt = s[c], up = s[8 + c];
-    if constexpr (NORM) {
+    if (p.norm) {
       gt *= rs;
       up *= rs;
     }
     y[c] = silu(gt) * up;
-    TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)m * p.ldy + j * 8 + c, y[c]);
+    if (p.Y) TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)m * p.ldy + j * 8 + c, y[c]);
   }
   frag_st_run<T>(p.yf, m, j * 8, y, 8);
 }
 
-// The gate/up projection between SPLIT_MIN_ROWS and SWIGLU_SPLIT_MAX_ROWS
-// rows, when K parts (the weight-streaming kernel's ranges) lower the bytes
-// the busiest compute unit streams by a sixth or more: for the 8B shape at
-// 64-256 rows the single-part launch puts two 4-strip workgroups on half the
-// units, the split one two 8-strip half-K workgroups on every unit (a third
-// fewer bytes each, against the parts' round trip).
-template <typename T>
-static hipError_t launch_swiglu_split(const GemmParams& p, hipStream_t st) {
-  const int ks = split_parts(EPI_SWIGLU, p.ntiles, p.ktiles);
-  GemmParams q = p;   // the parts read A (or its matrix-core-order copy); the reduce writes the copies
-  q.yf = q.y2f = FragOut{nullptr, 0, 0};
-  q.ksplit = ks;
-  q.norm = 0;
-  q.Y = p.part_ws;
-  q.ldy = p.ntiles * 16;
-  q.y_part = (size_t)p.M * q.ldy;
-  q.col0 = 0;
-  GemmShape sh{};
-  sh.waves = 1;   // one K range per part
-  hipError_t e = launch_tile<T, EPI_STORE_F32, false>(q, sh, ks, st);
-  if (e != hipSuccess) return e;
-  const dim3 grid((p.ntiles + 255) / 256, p.M);
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, p, p.part_ws, q.y_part, ks, q.ldy);
-    return hipGetLastError();
-  };
-  // the part count as a template argument where it is one of the wave counts, so all loads are in flight at once
-  if (p.norm) {
-    if (ks == 2) return go(swiglu_reduce_kernel<T, true, 2>);
-    if (ks == 4) return go(swiglu_reduce_kernel<T, true, 4>);
-    if (ks == 8) return go(swiglu_reduce_kernel<T, true, 8>);
-    return go(swiglu_reduce_kernel<T, true, 0>);
-  }
-  if (ks == 2) return go(swiglu_reduce_kernel<T, false, 2>);
-  if (ks == 4) return go(swiglu_reduce_kernel<T, false, 4>);
-  if (ks == 8) return go(swiglu_reduce_kernel<T, false, 8>);
-  return go(swiglu_reduce_kernel<T, false, 0>);
-}
-
-// A narrow weight (O, down) at more than SPLIT_MIN_ROWS rows: the weight-
-// streaming kernel would re-read the whole A block from L2 for every strip
-// group, so the tiled kernel computes each of the weight-streaming kernel's K
-// ranges as a part of its own (fp32 partial sums, no row scale), and the
-// reduce kernel adds them and applies the residual epilogue.
-template <typename T>
-static hipError_t launch_resid_split(const GemmParams& p, hipStream_t st) {
-  const int ks = split_parts(EPI_RESID, p.ntiles, p.ktiles);
-  GemmParams q = p;   // the parts read A (or its matrix-core-order copy); the reduce writes the copies
-  q.yf = q.y2f = FragOut{nullptr, 0, 0};
-  q.ksplit = ks;
-  q.Y = p.part_ws;
-  q.ldy = p.ntiles * 16;
-  q.y_part = (size_t)p.M * q.ldy;
-  q.R = nullptr;
-  q.Y2 = nullptr;
-  q.ssq_out = nullptr;
-  q.col0 = 0;
-  GemmShape sh{};
-  sh.waves = 1;   // one K range per part
-  hipError_t e = launch_tile<T, EPI_STORE_F32, false>(q, sh, ks, st);
-  if (e != hipSuccess) return e;
-  const int items = p.M * p.ntiles;
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((items + 255) / 256), dim3(256), 0, st, p.part_ws, q.y_part, ks, p.M, q.ldy,
-                       reinterpret_cast<const T*>(p.R), p.ldr, reinterpret_cast<T*>(p.Y), p.ldy,
-                       reinterpret_cast<T*>(p.Y2), p.ldy2, p.ssq_out, p.ssq_out_ld, 0, p.yf, p.y2f);
-    return hipGetLastError();
-  };
-  if (ks == 2) return go(resid_reduce_kernel<T, 2>);
-  if (ks == 4) return go(resid_reduce_kernel<T, 4>);
-  if (ks == 8) return go(resid_reduce_kernel<T, 8>);
-  return go(resid_reduce_kernel<T, 0>);
-}
-
-// Range split of the narrow drafter-side projections (W_c, relay MLP,
-// drafter context K/V: plain, fp32, bias + SiLU and bias epilogues) between
-// SPLIT_MIN_ROWS + 1 and SWIGLU_SPLIT_MAX_ROWS rows, where a tiled launch
-// would have too few workgroups and the weight-streaming kernel re-reads the
-// whole A block for every strip group: the tiled kernel computes each of the
-// weight-streaming kernel's wave ranges as a part of its own, and this kernel
-// folds the parts in range order from +0 -- that kernel's wave fold -- and
-// applies its epilogue.  One workgroup row per output row (every 16-lane group
-// computes the row scale); four columns per thread.
-template <typename T, int EPI, bool NORM, int KS>
+// Plain, fp32, bias + SiLU and bias epilogues: four columns per thread.
+template <typename T, int EPI, int KS>
 __global__ void __launch_bounds__(256) range_reduce_kernel(GemmParams p, const float* part, size_t part_stride,
                                                            int nw, int N) {
   const int m = blockIdx.y;
-  float rs = 1.f;
-  if constexpr (NORM) rs = norm_row_scale(p, m, threadIdx.x & 15);
   const int c4 = blockIdx.x * 256 + threadIdx.x;
   if (c4 >= N / 4) return;
+  const float rs = p.norm ? p.rs[m] : 1.f;
   float s[4] = {0.f, 0.f, 0.f, 0.f};
   const float* src = part + (size_t)m * N + 4 * c4;
   if constexpr (KS > 0) {   // all parts' loads in flight at once, summed in part order
@@ -943,14 +612,14 @@ __global__ void __launch_bounds__(256) range_reduce_kernel(GemmParams p, const f
   for (int i = 0; i < 4; ++i) {
     const int col = 4 * c4 + i;
     float v = s[i];
-    if constexpr (NORM) v *= rs;
+    if (p.norm) v *= rs;
     if constexpr (EPI == EPI_STORE_T) {
       TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)m * p.ldy + col, v);
     } else if constexpr (EPI == EPI_STORE_F32) {
       reinterpret_cast<float*>(p.Y)[(size_t)m * p.ldy + col] = v;
     } else if constexpr (EPI == EPI_BIAS_SILU) {
       v += TT<T>::ld(reinterpret_cast<const T*>(p.bias), col);
-      TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)m * p.ldy + col, silu(v));
+      if (p.Y) TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)m * p.ldy + col, silu(v));
       frag_st<T>(p.yf, m, col, silu(v));
     } else if constexpr (EPI == EPI_BIAS_F32) {
       v += TT<T>::ld(reinterpret_cast<const T*>(p.bias), col);
@@ -959,89 +628,109 @@ __global__ void __launch_bounds__(256) range_reduce_kernel(GemmParams p, const f
   }
 }
 
-bool range_split_applies(int epi, int M, int ntiles, int ksplit) {
-  return (epi == EPI_STORE_T || epi == EPI_STORE_F32 || epi == EPI_BIAS_SILU || epi == EPI_BIAS_F32) &&
-         ksplit <= 1 && M > SPLIT_MIN_ROWS && M <= SWIGLU_SPLIT_MAX_ROWS && (ntiles + TILE_BS - 1) / TILE_BS < 96;
-}
-
-template <typename T, int EPI, bool NORM>
-static hipError_t launch_range_reduce(const GemmParams& p, size_t part_stride, int nw, int N, hipStream_t st) {
-  const dim3 grid((N / 4 + 255) / 256, p.M);
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, p, p.part_ws, part_stride, nw, N);
-    return hipGetLastError();
-  };
-  if (nw == 2) return go(range_reduce_kernel<T, EPI, NORM, 2>);
-  if (nw == 4) return go(range_reduce_kernel<T, EPI, NORM, 4>);
-  if (nw == 8) return go(range_reduce_kernel<T, EPI, NORM, 8>);
-  return go(range_reduce_kernel<T, EPI, NORM, 0>);
-}
-
-template <typename T>
-static hipError_t launch_range_split(int epi, const GemmParams& p, hipStream_t st) {
+// A launch's K parts: one (the tiles fold the ranges) or, where that leaves
+// compute units idle, one per range (fp32 partial sums to part_ws, folded by a
+// reduce kernel), whichever is estimated faster.  A reduce takes about 4 us
+// plus its bytes at 6.5 TB/s (measured: four parts of 128 x 4096 5 us, of 1024
+// x 4096 14.7 us), and so do the partial sums' writes.
+static int tile_parts(int epi, const GemmParams& p) {
   const int nw = split_parts(epi, p.ntiles, p.ktiles);
-  GemmParams q = p;   // the parts read A (or its matrix-core-order copy); the reduce writes the copies
+  if (nw < 2 || !p.part_ws || (epi != EPI_RESID && p.M > split_max_rows(epi))) return 1;
+  const int cus = p.cus > 0 ? p.cus : 256;
+  double whole, split;
+  pick_tile(p.M, p.ntiles, p.ktiles, 1, cus, &whole);
+  pick_tile(p.M, p.ntiles, p.ktiles, nw, cus, &split);
+  const double part_us = (double)p.M * p.ntiles * 16 * 4 / 6.5e6;   // one part's sums, once over memory
+  const double fold1 = epi == EPI_RESID ? 4.0 + 2.0 * part_us : 0.0;
+  return split + 4.0 + 2.0 * nw * part_us < whole + fold1 ? nw : 1;
+}
+
+// fp32 partial sums of ks parts (each folding `waves` ranges) to part_ws
+template <typename T>
+static hipError_t launch_parts(const GemmParams& p, int waves, int ks, GemmParams* q_out, hipStream_t st) {
+  GemmParams q = p;   // the parts read A's matrix-core-order copy; the reduce writes the outputs
   q.yf = q.y2f = FragOut{nullptr, 0, 0};
-  q.ksplit = nw;
+  q.ksplit = ks;
   q.norm = 0;
   q.Y = p.part_ws;
   q.ldy = p.ntiles * 16;
   q.y_part = (size_t)p.M * q.ldy;
-  q.R = nullptr;
-  q.Y2 = nullptr;
-  q.ssq_out = nullptr;
   q.col0 = 0;
-  GemmShape sh{};
-  sh.waves = 1;   // one range per part
-  hipError_t e = launch_tile<T, EPI_STORE_F32, false>(q, sh, nw, st);
-  if (e != hipSuccess) return e;
-  const bool n = p.norm != 0;
+  *q_out = q;
+  return launch_tile<T, EPI_STORE_F32>(q, waves, ks, st);
+}
+
+// the part count as a template argument where it is one or a wave count, so all loads are in flight at once
+template <typename F>
+static hipError_t with_parts(int ks, F&& go) {
+  if (ks == 1) return go(std::integral_constant<int, 1>{});
+  if (ks == 2) return go(std::integral_constant<int, 2>{});
+  if (ks == 4) return go(std::integral_constant<int, 4>{});
+  if (ks == 8) return go(std::integral_constant<int, 8>{});
+  return go(std::integral_constant<int, 0>{});
+}
+
+template <typename T, int EPI>
+static hipError_t launch_range_reduce(const GemmParams& p, const GemmParams& q, int ks, hipStream_t st) {
+  return with_parts(ks, [&](auto k) {
+    hipLaunchKernelGGL((range_reduce_kernel<T, EPI, decltype(k)::value>), dim3((q.ldy / 4 + 255) / 256, p.M), dim3(256),
+                       0, st, p, p.part_ws, q.y_part, ks, q.ldy);
+    return hipGetLastError();
+  });
+}
+
+template <typename T>
+static hipError_t launch_many(int epi, const GemmParams& p, hipStream_t st) {
+  const int ks = p.ksplit > 1 ? p.ksplit : 1;
+  const int waves = gemm_shape(p.ntiles, p.ktiles, epi, ks).waves;
+  if (ks > 1) return epi == EPI_STORE_F32 ? launch_tile<T, EPI_STORE_F32>(p, waves, ks, st) : hipErrorInvalidValue;
+  const int parts = epi == EPI_ARGMAX ? 1 : tile_parts(epi, p);
+  GemmParams q;
+  hipError_t e;
+  if (epi == EPI_RESID) {
+    // the whole row's scale goes with the residual epilogue, so it always runs on the folded sums
+    if (p.norm || p.col0 || !p.part_ws || !p.ssq_out || !p.rs_out) return hipErrorInvalidValue;
+    if ((e = launch_parts<T>(p, parts > 1 ? 1 : waves, parts, &q, st)) != hipSuccess) return e;
+    const int threads = p.ntiles < 256 ? (p.ntiles + 63) / 64 * 64 : 256;
+    return with_parts(parts, [&](auto k) {
+      hipLaunchKernelGGL((resid_reduce_kernel<T, decltype(k)::value>), dim3(p.M), dim3(threads), 0, st, p.part_ws,
+                         q.y_part, parts, q.ldy, reinterpret_cast<const T*>(p.R), p.ldr, reinterpret_cast<T*>(p.Y),
+                         p.ldy, reinterpret_cast<T*>(p.Y2), p.ldy2, p.ssq_out, p.ssq_out_ld, p.rs_out, p.eps, p.yf,
+                         p.y2f);
+      return hipGetLastError();
+    });
+  }
+  if (parts > 1) {
+    if ((e = launch_parts<T>(p, 1, parts, &q, st)) != hipSuccess) return e;
+    switch (epi) {
+      case EPI_STORE_T: return launch_range_reduce<T, EPI_STORE_T>(p, q, parts, st);
+      case EPI_STORE_F32: return launch_range_reduce<T, EPI_STORE_F32>(p, q, parts, st);
+      case EPI_BIAS_SILU: return launch_range_reduce<T, EPI_BIAS_SILU>(p, q, parts, st);
+      case EPI_BIAS_F32: return launch_range_reduce<T, EPI_BIAS_F32>(p, q, parts, st);
+      case EPI_SWIGLU:
+        return with_parts(parts, [&](auto k) {
+          hipLaunchKernelGGL((swiglu_reduce_kernel<T, decltype(k)::value>), dim3((p.ntiles + 255) / 256, p.M),
+                             dim3(256), 0, st, p, p.part_ws, q.y_part, parts, q.ldy);
+          return hipGetLastError();
+        });
+    }
+    return hipErrorInvalidValue;
+  }
   switch (epi) {
-    case EPI_STORE_T:
-      return n ? launch_range_reduce<T, EPI_STORE_T, true>(p, q.y_part, nw, q.ldy, st)
-               : launch_range_reduce<T, EPI_STORE_T, false>(p, q.y_part, nw, q.ldy, st);
-    case EPI_STORE_F32:
-      return n ? launch_range_reduce<T, EPI_STORE_F32, true>(p, q.y_part, nw, q.ldy, st)
-               : launch_range_reduce<T, EPI_STORE_F32, false>(p, q.y_part, nw, q.ldy, st);
-    case EPI_BIAS_SILU:
-      return n ? hipErrorInvalidValue : launch_range_reduce<T, EPI_BIAS_SILU, false>(p, q.y_part, nw, q.ldy, st);
-    case EPI_BIAS_F32:
-      return n ? hipErrorInvalidValue : launch_range_reduce<T, EPI_BIAS_F32, false>(p, q.y_part, nw, q.ldy, st);
+    case EPI_STORE_T: return launch_tile<T, EPI_STORE_T>(p, waves, 1, st);
+    case EPI_STORE_F32: return launch_tile<T, EPI_STORE_F32>(p, waves, 1, st);
+    case EPI_SWIGLU: return launch_tile<T, EPI_SWIGLU>(p, waves, 1, st);
+    case EPI_BIAS_SILU: return launch_tile<T, EPI_BIAS_SILU>(p, waves, 1, st);
+    case EPI_BIAS_F32: return launch_tile<T, EPI_BIAS_F32>(p, waves, 1, st);
+    case EPI_ARGMAX: return launch_tile<T, EPI_ARGMAX>(p, waves, 1, st);
   }
   return hipErrorInvalidValue;
 }
 
-// Bytes the busiest compute unit streams in a tiled launch with ks K parts:
-// workgroups per unit (rounded up) x (A and W bytes of one workgroup's k
-// tiles), with the strip count launch_tile would pick.
-static double tile_unit_bytes(int ntiles, int ktiles, int M, int ks, int cus, int kt_bytes) {
-  const int mt = (M + TILE_BM - 1) / TILE_BM;
-  const int bs = (ntiles + TILE_BS - 1) / TILE_BS * ks * mt < 256 ? 4 : 8;
-  const long long wgs = (long long)((ntiles + bs - 1) / bs) * ks * mt;
-  const int kpart = (ktiles + ks - 1) / ks;
-  const double per_wg = (double)kpart * (TILE_BM + bs * 16) * kt_bytes;
-  return (double)((wgs + cus - 1) / cus) * per_wg;
-}
-
-template <typename T>
-static bool swiglu_split_pays(const GemmParams& p) {
-  if (p.cus < 1) return false;
-  const int ks = split_parts(EPI_SWIGLU, p.ntiles, p.ktiles);
-  if (ks < 2) return false;
-  const int ktb = TT<T>::KT * (int)sizeof(T);   // bytes of one row's k tile
-  return tile_unit_bytes(p.ntiles, p.ktiles, p.M, ks, p.cus, ktb) <
-         (5.0 / 6.0) * tile_unit_bytes(p.ntiles, p.ktiles, p.M, 1, p.cus, ktb);
-}
-
 template <typename T>
 static hipError_t launch_t(int epi, const GemmParams& p, hipStream_t st) {
+  if (p.M > SPLIT_MIN_ROWS) return launch_many<T>(epi, p, st);
   const int ks = p.ksplit > 1 ? p.ksplit : 1;
-  if (epi == EPI_RESID && p.M > SPLIT_MIN_ROWS && p.part_ws && !p.norm && p.col0 == 0)
-    return launch_resid_split<T>(p, st);
-  if (epi == EPI_SWIGLU && p.M > SPLIT_MIN_ROWS && p.M <= SWIGLU_SPLIT_MAX_ROWS && p.part_ws && p.col0 == 0 &&
-      swiglu_split_pays<T>(p))
-    return launch_swiglu_split<T>(p, st);
-  if (p.part_ws && p.col0 == 0 && range_split_applies(epi, p.M, p.ntiles, ks)) return launch_range_split<T>(epi, p, st);
   if (ks > 1 && epi != EPI_STORE_F32) return hipErrorInvalidValue;   // only partial fp32 outputs are split
   const GemmShape sh = gemm_shape(p.ntiles, p.ktiles, epi, ks);
   switch (epi) {

@@ -87,7 +87,7 @@ struct RopeParams {
 };
 
 hipError_t launch_embed(bool bf16, const int* tok, int M, const void* E, int V, int d, void* out, int* status,
-                        float* ssq, int ssq_ld, FragOut of, hipStream_t s);
+                        float* ssq, int ssq_ld, float* rs_out, float eps, FragOut of, hipStream_t s);
 hipError_t launch_rmsnorm(bool bf16, bool in_f32, const void* x, int ldx, int M, int d, const void* g, float eps,
                           void* out, int ldo, FragOut of, hipStream_t s);
 hipError_t launch_qk_rope_write(bool bf16, const RopeParams& p, hipStream_t s);
@@ -104,7 +104,7 @@ hipError_t launch_relay_gather(bool bf16, int carry_on, const int* carry_rec, co
 hipError_t launch_relay_input(bool bf16, int carry_on, const int* carry_rec, const int* anchor, const void* E,
                               const void* e_mask, const void* f, const float* bg, const void* ln_g,
                               const void* ln_b, float ln_eps, int nseq, int B, int d, int V, void* x, int* status,
-                              float* ssq, int ssq_ld, FragOut of, hipStream_t s);
+                              float* ssq, int ssq_ld, float* rs_out, float rms_eps, FragOut of, hipStream_t s);
 hipError_t launch_commit(const int* accept_len, int nseq, int* seq_len, hipStream_t s);
 hipError_t launch_force(const int* traj, int traj_stride, int traj_len, const signed char* mode, const int* tok,
                         const int* anchor, const int* start_pos, int nseq, int B, int V, int* block_tok,

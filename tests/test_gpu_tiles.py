@@ -1,0 +1,52 @@
+"""The tiled GEMM against the weight-streaming one (GPU property, no oracle):
+a prompt processed in chunks of at most 48 rows takes the weight-streaming
+kernels, larger chunks the tiles, their K parts and the reduce kernels, and
+every row's arithmetic is the same in both, so the target KV and the drafter
+context must agree bit for bit.  The chunk sizes sit at the edges of the tiles
+(64 and 128 rows), of the split rules (49, 256/257, 512/513 rows) and off the
+16-row tiles; the widths give odd strip and k-tile counts, K ranges of unequal
+length and reductions shorter than the load ring."""
+import numpy as np
+import pytest
+
+from workload import get_config
+from workload.configs import ModelDims
+from workload.synth import make_weights
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+DIMS = {
+    "bf16": get_config("small-bf16").dims,
+    "f32": get_config("small-f32").dims,
+    # 3, 4 and 5 k tiles per projection, 17 strips of vocabulary
+    "bf16-narrow": ModelDims("bf16", 96, 2, 2, 1, 64, 160, 272, 1, (0, 1)),
+    "f32-narrow": ModelDims("f32", 48, 2, 2, 1, 64, 112, 272, 1, (0, 1)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(DIMS))
+def test_chunk_rows_bitwise(name):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_06498_amd import Runtime
+    dims = DIMS[name]
+    r = np.random.default_rng(7)
+    prompts = [r.integers(0, dims.vocab, size=n).astype(np.int32) for n in (1100, 310)]
+    tok = torch.from_numpy(np.concatenate(prompts)).cuda()
+    w = make_weights(dims, 11)
+    ref = None
+    for rows in (48, 49, 64, 65, 127, 129, 200, 256, 257, 384, 512, 513, 1024):
+        print(f"[tiles] {name} rows={rows}", flush=True)
+        rt = Runtime(dims, 16, 2, 1200, w, max_rows=rows)
+        first = torch.zeros(2, dtype=torch.int32, device="cuda")
+        rt.prefill_batch(tok, [len(p) for p in prompts], first)
+        assert rt.status() == 0
+        got = [x.clone() for x in (rt.k_pool, rt.v_pool, rt.ck_pool, rt.cv_pool, first)]
+        rt.close()
+        if ref is None:
+            ref = got
+            assert any(bool((x != 0).any()) for x in ref)
+            continue
+        for i, (a, b) in enumerate(zip(ref, got)):
+            assert torch.equal(a, b), f"{name}: output {i} with {rows}-row chunks differs from 48-row chunks"
