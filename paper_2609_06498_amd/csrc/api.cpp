@@ -46,7 +46,7 @@ struct dflow_ctx {
   int KT;
   int q_dim, kv_dim, qkv_n;
   int mmax, rows_round;
-  int G, nsplit, part_items;
+  int G, nsplit;
   int split_keys;            // keys per attention chunk (split_keys_for)
   int round_chunks;          // attention chunks per split in the round calls (prefill: 1)
   int lm_groups;
@@ -60,9 +60,10 @@ struct dflow_ctx {
 
   void* ws = nullptr;         // caller-owned workspace (dflow_workspace_bytes)
   size_t ws_bytes = 0;
+  int prefill_keys = 0;            // keys up to the end of the prefill chunk being issued (host plan)
   int phase = DFLOW_PHASE_OTHER;   // entry point being issued (tags the kernel-timing record)
   // workspace views
-  void *x, *xn, *qkv, *q, *attn, *act, *hcap, *f, *fpre, *u, *hid;
+  void *x, *xn, *qkv, *q, *act, *hcap, *f, *fpre, *u, *hid;
   float *fproj, *bg, *part_o, *part_ml;
   float2* rope;
   uint64_t* amax;
@@ -159,7 +160,7 @@ struct Layout {
 };
 
 // Workspace carve-up; identical for dflow_workspace_bytes and dflow_create.
-Layout plan(const dflow_dims* d, int* nsplit_out, int* part_items_out, int* lm_groups_out) {
+Layout plan(const dflow_dims* d, int* nsplit_out, int* lm_groups_out) {
   const size_t elt = d->dtype == DFLOW_BF16 ? 2 : 4;
   const int qd = d->n_heads * d->head_dim, kvd = d->n_kv_heads * d->head_dim;
   const int qkvn = qd + 2 * kvd;
@@ -168,9 +169,11 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* part_items_out, int* lm_g
   const int G = d->n_heads / d->n_kv_heads;
   const int split_keys = split_keys_for(d->dtype == DFLOW_BF16, d->max_batch, d->n_kv_heads, d->max_pages * PAGE);
   const int nsplit = (d->max_pages * PAGE + split_keys - 1) / split_keys;
-  const int rg_round = (d->block * G + 15) / 16, rg_pre = (d->max_rows * G + 15) / 16;
-  int items = d->max_batch * rg_round;
-  if (rg_pre > items) items = rg_pre;
+  // attention partials: (16-row group, split) items per kv head of a round and of a prefill chunk
+  const size_t rg_round = (d->block * G + 15) / 16, rg_pre = (d->max_rows * G + 15) / 16;
+  size_t items = d->max_batch * rg_round * nsplit;
+  const size_t pre = rg_pre * ((d->max_pages * PAGE + PREFILL_SPLIT - 1) / PREFILL_SPLIT);
+  if (pre > items) items = pre;
   const int lm_groups = (d->vocab / 16 + 1) / 2;   // gemm_shape: two strips per argmax workgroup
   Layout L;
   size_t o = 0;
@@ -180,15 +183,15 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* part_items_out, int* lm_g
   add((size_t)mmax * 3 * d->d * elt);                  // 1 xn (also relay u rows)
   add((size_t)2 * mmax * qkvn * 4);                    // 2 qkv: up to two fp32 K parts
   add((size_t)mmax * qd * elt);                        // 3 q
-  add((size_t)mmax * qd * elt);                        // 4 attn
+  add(0);                                              // 4 unused
   add((size_t)mmax * (d->ffn > d->relay_hidden ? d->ffn : d->relay_hidden) * elt);  // 5 act / relay hidden
   add((size_t)mmax * d->n_capture * d->d * elt);       // 6 hcap
   add((size_t)rows_round * d->d * elt);                // 7 f (projected features of the last verify)
   add((size_t)mmax * d->d * elt);                      // 8 fpre (prefill features)
   add((size_t)mmax * d->d * 4);                        // 9 fproj
   add((size_t)rows_round * 2 * d->d * 4);              // 10 bg
-  add((size_t)items * d->n_kv_heads * nsplit * 16 * d->head_dim * 4);  // 11 part_o
-  add((size_t)items * d->n_kv_heads * nsplit * 32 * 4);               // 12 part_ml
+  add(items * d->n_kv_heads * 16 * d->head_dim * 4);    // 11 part_o
+  add(items * d->n_kv_heads * 32 * 4);                  // 12 part_ml
   add((size_t)d->max_pages * PAGE * (d->head_dim / 2) * sizeof(float2));  // 13 rope
   add((size_t)lm_groups * mmax * 8);                   // 14 amax: [lm_groups][rows] argmax keys
   add((size_t)d->max_batch * CARRY_REC * 4);           // 15 carry_rec
@@ -230,7 +233,6 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* part_items_out, int* lm_g
   add((size_t)mmax * 4);                                  // 33 rs: RMSNorm row scales
   L.total = o;
   if (nsplit_out) *nsplit_out = nsplit;
-  if (part_items_out) *part_items_out = items;
   if (lm_groups_out) *lm_groups_out = lm_groups;
   return L;
 }
@@ -239,7 +241,7 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* part_items_out, int* lm_g
 
 extern "C" size_t dflow_workspace_bytes(const dflow_dims* dims) {
   if (validate(dims) != DFLOW_OK) return 0;
-  return plan(dims, nullptr, nullptr, nullptr).total;
+  return plan(dims, nullptr, nullptr).total;
 }
 
 extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, const dflow_cache* cache,
@@ -251,7 +253,7 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   if (((uintptr_t)workspace & 255) || ((uintptr_t)status & 3))
     return fail(DFLOW_EINVAL, "create: workspace must be 256-byte and status 4-byte aligned");
   {
-    const size_t need = plan(dims, nullptr, nullptr, nullptr).total;
+    const size_t need = plan(dims, nullptr, nullptr).total;
     if (workspace_bytes < need)
       return fail(DFLOW_ECAPACITY, "create: workspace of %zu bytes, %zu needed", workspace_bytes, need);
   }
@@ -298,7 +300,7 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   c->c = *cache;
   c->pool_layer_elems = (size_t)dims->num_pages * dims->n_kv_heads * PAGE * dims->head_dim;
 
-  Layout L = plan(dims, &c->nsplit, &c->part_items, &c->lm_groups);
+  Layout L = plan(dims, &c->nsplit, &c->lm_groups);
   c->split_keys = split_keys_for(c->bf, dims->max_batch, dims->n_kv_heads, dims->max_pages * PAGE);
   c->round_chunks = round_chunks_for(dims->max_batch, dims->n_kv_heads, dims->max_pages * PAGE, c->split_keys, c->cus);
   c->ws = workspace;
@@ -308,7 +310,6 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   c->xn = b + L.off[1];
   c->qkv = b + L.off[2];
   c->q = b + L.off[3];
-  c->attn = b + L.off[4];
   c->act = b + L.off[5];
   c->hcap = b + L.off[6];
   c->f = b + L.off[7];
@@ -464,7 +465,8 @@ hipError_t gemm(dflow_ctx* c, hipStream_t st, int epi, const void* A, int lda, c
 
 void* pool_layer(dflow_ctx* c, void* pool, int l) { return (char*)pool + (size_t)l * c->pool_layer_elems * c->elt; }
 
-// Attention of `nseq` sequences x Bq rows over one layer's pools.  With
+// Attention of `nseq` sequences x Bq rows over one layer's pools.  Prefill has
+// a kernel of its own (from c->q, keys and values already cached).  With
 // `fused`, from the raw QKV projection rows (QK-norm, RoPE and the block's
 // KV-cache write happen inside); otherwise from c->q after qk_rope.
 hipError_t attention(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int nseq, int Bq, const int* start_pos,
@@ -492,9 +494,14 @@ hipError_t attention(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int nse
   a.Hkv = c->dm.n_kv_heads;
   a.Dh = c->dm.head_dim;
   a.causal = causal;
-  {
+  const bool prefill = c->phase == DFLOW_PHASE_PREFILL;
+  if (prefill) {
+    a.split_keys = PREFILL_SPLIT;
+    a.nsplit = (c->prefill_keys + PREFILL_SPLIT - 1) / PREFILL_SPLIT;
+    a.row_splits = 1;
+  } else {
     const int nw = attention_waves(fused, Bq, c->G), nrg = (Bq * c->G + 15) / 16;
-    a.chunks = (c->phase != DFLOW_PHASE_PREFILL && nrg <= nw) ? c->round_chunks : 1;
+    a.chunks = nrg <= nw ? c->round_chunks : 1;
     a.split_keys = c->split_keys * a.chunks;
     a.nsplit = (c->dm.max_pages * PAGE + a.split_keys - 1) / a.split_keys;   // <= c->nsplit
   }
@@ -505,7 +512,7 @@ hipError_t attention(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int nse
   // per prefetched byte (8B shape, same box: O 4.400 -> 4.377 ms/round,
   // gate/up 4.392 -> 4.359; 1.7B shape: O 1.932 -> 1.897, gate/up 1.898 ->
   // 1.917, its shorter attention stretched by the larger prefetch).
-  if (c->phase != DFLOW_PHASE_PREFILL && L.wo && L.wgu && c->cus > nseq * a.Hkv * a.nsplit) {
+  if (!prefill && L.wo && L.wgu && c->cus > nseq * a.Hkv * a.nsplit) {
     const int idle = c->cus - nseq * a.Hkv * a.nsplit;
     const size_t cap = (size_t)idle * ATTN_PF_WG_BYTES;
     const size_t wo_bytes = (size_t)c->dm.d * c->q_dim * c->elt;
@@ -520,12 +527,12 @@ hipError_t attention(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int nse
   a.rg = (Bq * c->G + 15) / 16;
   a.part_o = c->part_o;
   a.part_ml = c->part_ml;
-  a.out = c->attn;
   a.outf = fout(c, c->attnf, c->q_dim);
   const bool rec = c->prof && c->n_ev < PROF_MAX;
   hipError_t e;
   if (rec && (e = hipEventRecord(c->ev0[c->n_ev], st)) != hipSuccess) return e;
-  if ((e = launch_attention(c->bf, a, st)) != hipSuccess) return e;
+  if ((e = prefill ? launch_attention_prefill(c->bf, a, c->cus, st) : launch_attention(c->bf, a, st)) != hipSuccess)
+    return e;
   if (rec) {
     if ((e = hipEventRecord(c->ev1[c->n_ev], st)) != hipSuccess) return e;
     c->ev_rec[c->n_ev++] = {CLS_ATTN, 0, 0, nseq * Bq, c->phase, 0.0};
@@ -589,7 +596,7 @@ hipError_t decoder_layer(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int
   if ((e = gemm(c, st, EPI_STORE_F32, c->x, d.d, L.wqkv, M, c->qkv_n, d.d, c->qkv, c->qkv_n, nullptr, 0, nullptr, 0,
                 nullptr, nullptr, 0, attn_n, nullptr, c->qkv_ks, fq)))
     return e;
-  const bool fused = attention_fuses_rope(c->bf, Bq, c->G, d.head_dim, c->split_keys);
+  const bool fused = c->phase != DFLOW_PHASE_PREFILL && attention_fuses_rope(c->bf, Bq, c->G, d.head_dim, c->split_keys);
   if (!fused) {
     RopeParams r = rope_params(c, L, nseq, Bq, d.n_heads, start_pos, nullptr, page_table, kpool, vpool);
     r.qkv32 = reinterpret_cast<const float*>(c->qkv);
@@ -598,7 +605,7 @@ hipError_t decoder_layer(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int
     if ((e = launch_qk_rope_write(c->bf, r, st))) return e;
   }
   if ((e = attention(c, st, L, nseq, Bq, start_pos, page_table, kpool, vpool, causal, fused))) return e;
-  if ((e = gemm(c, st, EPI_RESID, c->attn, c->q_dim, L.wo, M, d.d, c->q_dim, c->x, d.d, c->x, d.d, nullptr, 0,
+  if ((e = gemm(c, st, EPI_RESID, nullptr, c->q_dim, L.wo, M, d.d, c->q_dim, c->x, d.d, c->x, d.d, nullptr, 0,
                 nullptr, nullptr, 0, NormIn(), c->ssq, 1, fo)))
     return e;
   if ((e = gemm(c, st, EPI_SWIGLU, c->x, d.d, L.wgu, M, 2 * d.ffn, d.d, c->act, d.ffn, nullptr, 0, nullptr, 0,
@@ -730,6 +737,7 @@ int prefill_impl(dflow_ctx* c, hipStream_t st, int seq, const int32_t* tok, int 
   for (int p0 = 0; p0 < len; p0 += d.max_rows) {
     const int n = (len - p0) < d.max_rows ? (len - p0) : d.max_rows;
     const bool last = p0 + n >= len;
+    c->prefill_keys = p0 + n;
     HIPCHK(launch_set_int(c->tmp_pos, p0, st));
     HIPCHK(launch_embed(c->bf, tok + p0, n, c->w.embed, d.vocab, d.d, c->x, c->status, c->ssq, SSQ_LD,
                         c->rs, d.rms_eps, fout(c, c->xf, d.d), st));

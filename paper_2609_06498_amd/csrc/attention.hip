@@ -65,6 +65,12 @@ template <> struct Chunk<float> {
   __device__ static inline float elem(const u32x4_t& u, int i) { return __uint_as_float(u[i]); }
 };
 
+}  // namespace dflow
+
+#include "attn_prefill.h"
+
+namespace dflow {
+
 // Offsets of element (slot, e) of a page block in matrix-core fragment order.
 template <typename T, int DH>
 __device__ inline int kfrag_off(int slot, int e) {
@@ -658,7 +664,7 @@ __global__ void __launch_bounds__(DH) attn_combine_kernel(AttnParams p) {
   const int ar = j * G + g;
   const int rgi = ar >> 4, r = ar & 15;
   const int kv_len = p.start_pos[s] + p.Bq;
-  int ns = (kv_len + p.split_keys - 1) / p.split_keys;
+  int ns = p.row_splits ? (p.start_pos[s] + j) / p.split_keys + 1 : (kv_len + p.split_keys - 1) / p.split_keys;
   if (ns > p.nsplit) ns = p.nsplit;
   const size_t base = (((size_t)s * p.Hkv + kvh) * p.rg + rgi) * p.nsplit;
   const float* ml = p.part_ml + base * 32 + 2 * r;
@@ -675,7 +681,6 @@ __global__ void __launch_bounds__(DH) attn_combine_kernel(AttnParams p) {
     lsum += f * ml[(size_t)sp * 32 + 1];
   }
   const float v = lsum > 0.f ? acc / lsum : 0.f;
-  TT<T>::st(reinterpret_cast<T*>(p.out), (size_t)row * p.Hq * DH + hq * DH + d, v);
   frag_st<T>(p.outf, row, hq * DH + d, v);
 }
 
@@ -749,6 +754,45 @@ static hipError_t launch_dh(const AttnParams& p, hipStream_t st) {
   // one wave per 16-row group up to eight; beyond, waves take several groups
   if (p.Bq * (p.Hq / p.Hkv) <= 64) return launch_k<T, DH, 4, false, 1>(p, st);
   return launch_k<T, DH, 8, false, 1>(p, st);
+}
+
+template <typename T, int DH, int NW, int RG, int NS>
+static hipError_t launch_prefill_shape(const AttnParams& p, hipStream_t st) {
+  constexpr size_t lds = (size_t)NS * 2 * PAGE * DH * sizeof(T);
+  static const hipError_t attr = hipFuncSetAttribute(
+      reinterpret_cast<const void*>(&attn_prefill_kernel<T, DH, NW, RG, NS>),
+      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (attr != hipSuccess) return attr;
+  const int tiles = (p.rg + NW * RG - 1) / (NW * RG);
+  hipLaunchKernelGGL((attn_prefill_kernel<T, DH, NW, RG, NS>), dim3(tiles * p.Hkv * p.nsplit), dim3(NW * 64), lds, st,
+                     p, tiles);
+  return hipGetLastError();
+}
+
+template <typename T, int DH>
+static hipError_t launch_prefill_dh(const AttnParams& p, int cus, hipStream_t st) {
+  if (p.nseq != 1 || p.split_keys != PREFILL_SPLIT || p.nsplit < 1 || !p.outf.p) return hipErrorInvalidValue;
+  // Two row groups per wave share the LDS reads of a page (1.3 us a page and
+  // workgroup with two workgroups per unit, 830 TFLOP/s) once such workgroups
+  // outnumber the units; below that smaller ones use more of the chip (1.7B
+  // shape, 512 rows, 6 splits: 73 us against 82 at one group per wave; 3
+  // splits 54 against 46; one split 64-row tiles 25.3, 32-row tiles 24.1).
+  auto wgs = [&](int groups) { return (p.rg + groups - 1) / groups * p.Hkv * p.nsplit; };
+  hipError_t e;
+  if (wgs(8) > cus) e = launch_prefill_shape<T, DH, 4, 2, 2>(p, st);
+  else if (2 * wgs(4) > cus) e = launch_prefill_shape<T, DH, 4, 1, 2>(p, st);
+  else e = launch_prefill_shape<T, DH, 2, 1, 2>(p, st);
+  if (e != hipSuccess || p.nsplit == 1) return e;
+  hipLaunchKernelGGL((attn_combine_kernel<T, DH>), dim3(p.Bq, p.Hq), dim3(DH), 0, st, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_attention_prefill(bool bf16, const AttnParams& p, int cus, hipStream_t st) {
+  if (p.Dh == 128)
+    return bf16 ? launch_prefill_dh<dflow::bf16, 128>(p, cus, st) : launch_prefill_dh<float, 128>(p, cus, st);
+  if (p.Dh == 64)
+    return bf16 ? launch_prefill_dh<dflow::bf16, 64>(p, cus, st) : launch_prefill_dh<float, 64>(p, cus, st);
+  return hipErrorInvalidValue;
 }
 
 int attention_waves(bool fused, int Bq, int G) { return fused || Bq * G > 64 ? 8 : 4; }

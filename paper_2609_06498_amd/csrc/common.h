@@ -2,6 +2,10 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
+#include <utility>
+
 #include "gemm.h"
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -125,6 +129,14 @@ __device__ inline void frag_st_run(const FragOut& f, int m, int c, const float* 
   }
 }
 
+// 4 consecutive values of row m from column c (a multiple of 4, the producer's c0 too) to the copy
+template <typename T>
+__device__ inline void frag_st4(const FragOut& f, int m, int c, const float* v) {
+  T* o = reinterpret_cast<T*>(f.p) + afrag_off<T>(m, f.c0 + c, f.ktiles);
+  if constexpr (sizeof(T) == 2) *reinterpret_cast<uint2*>(o) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+  else *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
 template <typename T> struct Row16;
 template <> struct Row16<bf16> {
   __device__ static inline void load(const bf16* p, float* v) {
@@ -188,6 +200,28 @@ __device__ inline f32x4_t mma_frag(float, const uint4& a, const uint4& b, f32x4_
   acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
   acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
   return acc;
+}
+
+// ------------------------------------------------------------------ load to LDS
+// 64 lanes x 16 bytes from base + voff (voff per lane) to LDS bytes lds + OFF .. lds + OFF + 1023
+template <int OFF>
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const void* base, uint32_t voff) {
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base),
+               "n"(OFF)
+               : "memory", "scc");
+}
+// wait until at most N vector-memory operations of this wave are in flight and
+// its LDS reads are done, then meet the workgroup's other waves
+template <int N>
+__device__ __forceinline__ void wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+  (std::make_integer_sequence<int, N>{});
 }
 
 // Wave reductions (64 lanes)

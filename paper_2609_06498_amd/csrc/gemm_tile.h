@@ -22,34 +22,10 @@
 // are swapped (W first): a lane then holds four consecutive columns of one
 // row, and the epilogues store vectors straight from registers.
 #pragma once
-#include <type_traits>
-#include <utility>
-
 #include "common.h"
 #include "gemm.h"
 
 namespace dflow {
-
-// 64 lanes x 16 bytes from base + voff (voff per lane) to LDS bytes lds + OFF .. lds + OFF + 1023
-template <int OFF>
-__device__ __forceinline__ void load_to_lds(uint32_t lds, const void* base, uint32_t voff) {
-  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base),
-               "n"(OFF)
-               : "memory", "scc");
-}
-// wait until at most N vector-memory operations of this wave are in flight and
-// its LDS reads are done, then meet the workgroup's other waves
-template <int N>
-__device__ __forceinline__ void wait_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
-}
-
-// f(integral_constant<int, 0>) .. f(integral_constant<int, N - 1>)
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  [&]<int... I>(std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
-  (std::make_integer_sequence<int, N>{});
-}
 
 // two consecutive values (even column)
 template <typename T> __device__ __forceinline__ void pair_st(T* p, float a, float b);

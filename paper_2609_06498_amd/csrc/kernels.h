@@ -41,8 +41,8 @@ struct AttnParams {
   int rg;                    // 16-row groups per (seq, kv head)
   float* part_o;             // [nseq][Hkv][rg][nsplit][16][Dh]
   float* part_ml;            // [nseq][Hkv][rg][nsplit][16][2]
-  void* out;                 // [nseq*Bq, Hq*Dh] storage type
-  FragOut outf;              // matrix-core-order copy of out for the O projection (skinny launches)
+  int row_splits;            // 1: the combine merges the splits up to each row's own position (prefill)
+  FragOut outf;              // [nseq*Bq, Hq*Dh] output in matrix-core order, the O projection's operand
   // pf_wgs extra workgroups (after the nseq*Hkv*nsplit attention ones) read
   // bytes [0, pf_bytes) of pf, pf_per bytes each (multiples of 16), with
   // plain loads that leave them in the memory-side cache for a following
@@ -55,6 +55,13 @@ struct AttnParams {
 // stretched the launch by 0.5-0.9 us for less than that gained).
 constexpr size_t ATTN_PF_WG_BYTES = 192 * 1024;
 hipError_t launch_attention(bool bf16, const AttnParams& p, hipStream_t s);
+// Causal attention of one sequence's prefill chunk (p.Bq rows from p.q, keys
+// and values already in the cache); p.nsplit splits of PREFILL_SPLIT keys.  Large
+// enough that partials stay a small part of the traffic, small enough that a
+// long prompt's chunk fills the chip (512 rows of the 1.7B shape are 64 row
+// groups per kv head).
+constexpr int PREFILL_SPLIT = 2048;
+hipError_t launch_attention_prefill(bool bf16, const AttnParams& p, int cus, hipStream_t s);
 // Waves per attention workgroup (each owns one 16-row group; more groups need chunks = 1).
 int attention_waves(bool fused, int Bq, int G);
 // Whether the fused variant fits (block rows per wave, LDS) for this shape.

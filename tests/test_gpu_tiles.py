@@ -1,8 +1,11 @@
-"""The tiled GEMM against the weight-streaming one (GPU property, no oracle):
-a prompt processed in chunks of at most 48 rows takes the weight-streaming
-kernels, larger chunks the tiles, their K parts and the reduce kernels, and
-every row's arithmetic is the same in both, so the target KV and the drafter
-context must agree bit for bit.  The chunk sizes sit at the edges of the tiles
+"""The tiled GEMM against the weight-streaming one, and prompt attention at every
+tile (GPU property, no oracle): a prompt processed in chunks of at most 48 rows
+takes the weight-streaming kernels, larger chunks the tiles, their K parts and
+the reduce kernels, and every row's arithmetic is the same in both, so the
+target KV and the drafter context must agree bit for bit.  The longer prompt
+crosses the first boundary of the attention splits (2048 keys), so its rows are
+written directly, or merged from one or two partials, depending on the chunk.
+  The chunk sizes sit at the edges of the tiles
 (64 and 128 rows), of the split rules (49, 256/257, 512/513 rows) and off the
 16-row tiles; the widths give odd strip and k-tile counts, K ranges of unequal
 length and reductions shorter than the load ring."""
@@ -32,13 +35,13 @@ def test_chunk_rows_bitwise(name):
     from paper_2609_06498_amd import Runtime
     dims = DIMS[name]
     r = np.random.default_rng(7)
-    prompts = [r.integers(0, dims.vocab, size=n).astype(np.int32) for n in (1100, 310)]
+    prompts = [r.integers(0, dims.vocab, size=n).astype(np.int32) for n in (2300, 310)]
     tok = torch.from_numpy(np.concatenate(prompts)).cuda()
     w = make_weights(dims, 11)
     ref = None
     for rows in (48, 49, 64, 65, 127, 129, 200, 256, 257, 384, 512, 513, 1024):
         print(f"[tiles] {name} rows={rows}", flush=True)
-        rt = Runtime(dims, 16, 2, 1200, w, max_rows=rows)
+        rt = Runtime(dims, 16, 2, 2400, w, max_rows=rows)
         first = torch.zeros(2, dtype=torch.int32, device="cuda")
         rt.prefill_batch(tok, [len(p) for p in prompts], first)
         assert rt.status() == 0
