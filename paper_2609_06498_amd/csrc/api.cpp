@@ -200,7 +200,7 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* lm_groups_out) {
   add((size_t)mmax * 4);                               // 18 tmp_argmax
   add((size_t)mmax * SSQ_LD * 4);                      // 19 ssq: per-strip sums of squares of the residual rows
   add((size_t)ARGMAX_SPLITS * mmax * 8);               // 20 amax_part: [split][row] partial argmax keys
-  add(256);                                            // 21 counters (zero between launches)
+  add(ARGMAX_BLOCKS * 4);                              // 21 counters (zero between launches)
   add((size_t)mmax * d->n_draft_layers * 2 * kvd * elt);   // 22 ctxkv: drafter-context K/V rows of all drafter layers
   add((size_t)(d->n_draft_layers > 0 ? d->n_draft_layers : 1) * sizeof(void*));   // 23 drafter K-norm gain pointers
   add(samp_workspace_bytes(d->vocab, mmax, d->max_batch));   // 24 sampling partials (log-sum-exp, draw keys)
