@@ -63,7 +63,7 @@ struct dflow_ctx {
   int prefill_keys = 0;            // keys up to the end of the prefill chunk being issued (host plan)
   int phase = DFLOW_PHASE_OTHER;   // entry point being issued (tags the kernel-timing record)
   // workspace views
-  void *x, *xn, *qkv, *q, *act, *hcap, *f, *fpre, *u, *hid;
+  void *x, *qkv, *q, *hcap, *f;
   float *fproj, *bg, *part_o, *part_ml;
   float2* rope;
   uint64_t* amax;
@@ -180,14 +180,14 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* lm_groups_out) {
   int i = 0;
   auto add = [&](size_t bytes) { L.off[i++] = o; o += align256(bytes); };
   add((size_t)mmax * d->d * elt);                      // 0 x
-  add((size_t)mmax * 3 * d->d * elt);                  // 1 xn (also relay u rows)
+  add(0);                                              // 1 unused
   add((size_t)2 * mmax * qkvn * 4);                    // 2 qkv: up to two fp32 K parts
   add((size_t)mmax * qd * elt);                        // 3 q
   add(0);                                              // 4 unused
-  add((size_t)mmax * (d->ffn > d->relay_hidden ? d->ffn : d->relay_hidden) * elt);  // 5 act / relay hidden
-  add((size_t)mmax * d->n_capture * d->d * elt);       // 6 hcap
+  add(0);                                              // 5 unused
+  add((size_t)mmax * d->n_capture * d->d * elt);       // 6 hcap (row-major copy, when the caller asks for it)
   add((size_t)rows_round * d->d * elt);                // 7 f (projected features of the last verify)
-  add((size_t)mmax * d->d * elt);                      // 8 fpre (prefill features)
+  add(0);                                              // 8 unused
   add((size_t)mmax * d->d * 4);                        // 9 fproj
   add((size_t)rows_round * 2 * d->d * 4);              // 10 bg
   add(items * d->n_kv_heads * 16 * d->head_dim * 4);    // 11 part_o
@@ -307,13 +307,10 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   c->ws_bytes = L.total;
   char* b = (char*)c->ws;
   c->x = b + L.off[0];
-  c->xn = b + L.off[1];
   c->qkv = b + L.off[2];
   c->q = b + L.off[3];
-  c->act = b + L.off[5];
   c->hcap = b + L.off[6];
   c->f = b + L.off[7];
-  c->fpre = b + L.off[8];
   c->fproj = (float*)(b + L.off[9]);
   c->bg = (float*)(b + L.off[10]);
   c->part_o = (float*)(b + L.off[11]);
@@ -339,8 +336,6 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   c->uf = b + L.off[31];
   c->ff = b + L.off[32];
   c->rs = (float*)(b + L.off[33]);
-  c->u = c->xn;
-  c->hid = c->act;
 
   // RoPE table: angle p * theta^(-2i/Dh) evaluated in double
   const int half = dims->head_dim / 2;
@@ -582,8 +577,11 @@ hipError_t decoder_layer(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int
   ffn_n.ssq = c->ssq;
   // QKV projection as fp32 partial sums over qkv_ks K parts (spreads the
   // weight stream evenly over the compute units); its consumers add them
-  // matrix-core-order operands: x from its producer, the
-  // attention output from the combine kernel, the SwiGLU output from gate/up
+  // matrix-core-order operands: x from its producer, the attention output
+  // from the combine kernel, the SwiGLU output from gate/up.  Projections read
+  // nothing else of their operand, so no row-major copy is written beside it
+  // (except x, which the residual sums read): the gate/up launch of 1024 rows of the
+  // Qwen3-8B shape writes 25 MB less.
   Frag fq, fo, fgu, fdn;
   fq.a = c->xf;
   fo.a = c->attnf;
@@ -608,19 +606,22 @@ hipError_t decoder_layer(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int
   if ((e = gemm(c, st, EPI_RESID, nullptr, c->q_dim, L.wo, M, d.d, c->q_dim, c->x, d.d, c->x, d.d, nullptr, 0,
                 nullptr, nullptr, 0, NormIn(), c->ssq, 1, fo)))
     return e;
-  if ((e = gemm(c, st, EPI_SWIGLU, c->x, d.d, L.wgu, M, 2 * d.ffn, d.d, c->act, d.ffn, nullptr, 0, nullptr, 0,
+  if ((e = gemm(c, st, EPI_SWIGLU, c->x, d.d, L.wgu, M, 2 * d.ffn, d.d, nullptr, d.ffn, nullptr, 0, nullptr, 0,
                 nullptr, nullptr, 0, ffn_n, nullptr, 1, fgu)))
     return e;
   const int capld = d.n_capture * d.d;
-  if ((e = gemm(c, st, EPI_RESID, c->act, d.ffn, L.wdown, M, d.d, d.ffn, c->x, d.d, c->x, d.d, capture, capld,
+  if ((e = gemm(c, st, EPI_RESID, nullptr, d.ffn, L.wdown, M, d.d, d.ffn, c->x, d.d, c->x, d.d, capture, capld,
                 nullptr, nullptr, 0, NormIn(), c->ssq, 1, fdn)))
     return e;
   return hipSuccess;
 }
 
-// Target forward over block rows already embedded in x; argmax of every row into `argmax_out`.
+// Target forward over block rows already embedded in x; argmax of every row
+// into `argmax_out`.  The captured states go to the matrix-core-order operand
+// of W_c, and with `rows_out` to the row-major c->hcap too.
 hipError_t target_forward(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const int* start_pos,
-                          const int* page_table, int* argmax_out, float* logits, int lm_row0 = 0, int lm_rows = -1) {
+                          const int* page_table, int* argmax_out, float* logits, bool rows_out, int lm_row0 = 0,
+                          int lm_rows = -1) {
   const dflow_dims& d = c->dm;
   const int M = nseq * Bq;
   hipError_t e;
@@ -630,7 +631,8 @@ hipError_t target_forward(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const 
     FragOut capf{nullptr, 0, 0};
     if (ci < d.n_capture && d.capture_layers[ci] == l) {
       capf = fout(c, c->hcapf, d.n_capture * d.d, ci * d.d);
-      cap = (char*)c->hcap + (size_t)ci++ * d.d * c->elt;
+      if (rows_out) cap = (char*)c->hcap + (size_t)ci * d.d * c->elt;
+      ++ci;
     }
     if ((e = decoder_layer(c, st, c->layers[l], nseq, Bq, start_pos, page_table, pool_layer(c, c->c.k_pool, l),
                            pool_layer(c, c->c.v_pool, l), 1, cap, capf)))
@@ -651,24 +653,24 @@ hipError_t target_forward(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const 
   return launch_argmax_reduce(c->amax, c->lm_groups, lm_rows, c->amax_part, c->counters, argmax_out, nullptr, st);
 }
 
-// F = RMSNorm(W_c [captured states]) for M rows -> fout (storage type)
+// F = RMSNorm(W_c [captured states]) for M rows -> c->ff and, row-major, out (null: no copy)
 hipError_t project(dflow_ctx* c, hipStream_t st, int M, void* out) {
   const dflow_dims& d = c->dm;
   hipError_t e;
   const int K = d.n_capture * d.d;
   Frag fr;
   fr.a = c->hcapf;
-  if ((e = gemm(c, st, EPI_STORE_F32, c->hcap, K, c->w.w_c, M, d.d, K, c->fproj, d.d, nullptr, 0, nullptr, 0,
+  if ((e = gemm(c, st, EPI_STORE_F32, nullptr, K, c->w.w_c, M, d.d, K, c->fproj, d.d, nullptr, 0, nullptr, 0,
                 nullptr, nullptr, 0, NormIn(), nullptr, 1, fr)))
     return e;
   return launch_rmsnorm(c->bf, true, c->fproj, d.d, M, d.d, c->w.g_c, d.rms_eps, out, d.d, fout(c, c->ff, d.d),
                         st);
 }
 
-// Drafter context K/V of feature rows (nseq x Bq) at start_pos + j for rows j <= row_limit[s].
+// Drafter context K/V of the feature rows in c->ff (nseq x Bq) at start_pos + j for rows j <= row_limit[s].
 // All drafter layers at once: one GEMM over the stacked [Wk; Wv] of every
 // layer, then K-norm + RoPE + paged write for every layer in one launch.
-hipError_t ctx_append(dflow_ctx* c, hipStream_t st, const void* feat, int nseq, int Bq, const int* start_pos,
+hipError_t ctx_append(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const int* start_pos,
                       const int* row_limit, const int* page_table) {
   const dflow_dims& d = c->dm;
   if (d.n_draft_layers < 1) return hipSuccess;
@@ -677,7 +679,7 @@ hipError_t ctx_append(dflow_ctx* c, hipStream_t st, const void* feat, int nseq, 
   hipError_t e;
   Frag fr;
   fr.a = c->ff;
-  if ((e = gemm(c, st, EPI_STORE_T, feat, d.d, c->w.draft_wkv_ctx, M, ncols, d.d, c->ctxkv, ncols, nullptr, 0,
+  if ((e = gemm(c, st, EPI_STORE_T, nullptr, d.d, c->w.draft_wkv_ctx, M, ncols, d.d, c->ctxkv, ncols, nullptr, 0,
                 nullptr, 0, nullptr, nullptr, 0, NormIn(), nullptr, 1, fr)))
     return e;
   RopeParams r{};
@@ -743,9 +745,9 @@ int prefill_impl(dflow_ctx* c, hipStream_t st, int seq, const int32_t* tok, int 
                         c->rs, d.rms_eps, fout(c, c->xf, d.d), st));
     int* amax = last && !smp ? c->tmp_argmax : nullptr;
     float* lrow = last && smp ? c->samp_row : nullptr;
-    HIPCHK(target_forward(c, st, 1, n, c->tmp_pos, pt, amax, lrow, n - 1, 1));
-    HIPCHK(project(c, st, n, c->fpre));
-    HIPCHK(ctx_append(c, st, c->fpre, 1, n, c->tmp_pos, nullptr, pt));
+    HIPCHK(target_forward(c, st, 1, n, c->tmp_pos, pt, amax, lrow, false, n - 1, 1));
+    HIPCHK(project(c, st, n, nullptr));
+    HIPCHK(ctx_append(c, st, 1, n, c->tmp_pos, nullptr, pt));
     if (last && !smp) HIPCHK(hipMemcpyAsync(first, c->tmp_argmax, 4, hipMemcpyDeviceToDevice, st));
   }
   if (smp) {
@@ -800,11 +802,11 @@ extern "C" int dflow_draft_block(dflow_ctx* c, hipStream_t st, int nseq, const i
     f1.a = c->uf;
     f1.y = fout(c, c->actf, d.relay_hidden);
     f2.a = c->actf;
-    HIPCHK(launch_relay_gather(c->bf, 1, c->carry_rec, c->w.embed, c->f, nseq, B, d.d, d.vocab, c->u,
+    HIPCHK(launch_relay_gather(c->bf, 1, c->carry_rec, c->w.embed, c->f, nseq, B, d.d, d.vocab,
                                fout(c, c->uf, 3 * d.d), st));
-    HIPCHK(gemm(c, st, EPI_BIAS_SILU, c->u, 3 * d.d, c->w.relay_w1, M, d.relay_hidden, 3 * d.d, c->hid,
+    HIPCHK(gemm(c, st, EPI_BIAS_SILU, nullptr, 3 * d.d, c->w.relay_w1, M, d.relay_hidden, 3 * d.d, nullptr,
                 d.relay_hidden, nullptr, 0, nullptr, 0, c->w.relay_c1, nullptr, 0, NormIn(), nullptr, 1, f1));
-    HIPCHK(gemm(c, st, EPI_BIAS_F32, c->hid, d.relay_hidden, c->w.relay_w2, M, 2 * d.d, d.relay_hidden, c->bg,
+    HIPCHK(gemm(c, st, EPI_BIAS_F32, nullptr, d.relay_hidden, c->w.relay_w2, M, 2 * d.d, d.relay_hidden, c->bg,
                 2 * d.d, nullptr, 0, nullptr, 0, c->w.relay_c2, nullptr, 0, NormIn(), nullptr, 1, f2));
   }
   HIPCHK(launch_relay_input(c->bf, carry_on ? 1 : 0, c->carry_rec, anchor_tok, c->w.embed, c->w.e_mask, c->f, c->bg,
@@ -835,7 +837,7 @@ extern "C" int dflow_verify_block(dflow_ctx* c, hipStream_t st, int nseq, const 
   const int B = d.block, M = nseq * B;
   HIPCHK(launch_embed(c->bf, block_tok, M, c->w.embed, d.vocab, d.d, c->x, c->status, c->ssq, SSQ_LD, c->rs,
                       d.rms_eps, fout(c, c->xf, d.d), st));
-  HIPCHK(target_forward(c, st, nseq, B, start_pos, c->c.page_table, tgt_argmax, logits));
+  HIPCHK(target_forward(c, st, nseq, B, start_pos, c->c.page_table, tgt_argmax, logits, hcap != nullptr));
   if (hcap)
     HIPCHK(hipMemcpyAsync(hcap, c->hcap, (size_t)M * d.n_capture * d.d * c->elt, hipMemcpyDeviceToDevice, st));
   return DFLOW_OK;
@@ -953,7 +955,7 @@ extern "C" int kv_commit(dflow_ctx* c, hipStream_t st, int nseq, const int32_t* 
   if (rc) return rc;
   if (!accept_len || !seq_len) return fail(DFLOW_EINVAL, "kv_commit: null argument");
   c->phase = DFLOW_PHASE_COMMIT;
-  HIPCHK(ctx_append(c, st, c->f, nseq, c->dm.block, seq_len, accept_len, c->c.page_table));
+  HIPCHK(ctx_append(c, st, nseq, c->dm.block, seq_len, accept_len, c->c.page_table));
   HIPCHK(launch_commit(accept_len, nseq, seq_len, st));
   return DFLOW_OK;
 }

@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const TI* x, int ldx, int 
 #pragma unroll
       for (int e = 0; e < VN; ++e) {
         y[e] = v[r][e] * rs * TT<T>::ld(g, (size_t)i * VN + e);
-        TT<T>::st(o, (size_t)i * VN + e, y[e]);
+        if (out) TT<T>::st(o, (size_t)i * VN + e, y[e]);
       }
       frag_st_run<T>(of, row, i * VN, y, VN);
     }
@@ -122,7 +122,7 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(const TI* x, int ldx, int 
 #pragma unroll
     for (int e = 0; e < VN; ++e) {
       y[e] = t[e] * rs * TT<T>::ld(g, (size_t)i * VN + e);
-      TT<T>::st(o, (size_t)i * VN + e, y[e]);
+      if (out) TT<T>::st(o, (size_t)i * VN + e, y[e]);
     }
     frag_st_run<T>(of, row, i * VN, y, VN);
   }
@@ -342,14 +342,13 @@ hipError_t launch_accept(const int* block, const int* g, int nseq, int B, int ca
 // u[s*B + i] = [E(b); E(y_rej); f[s*B + rec[1] + i - 1]] for relayed block indices rec[4]..rec[0], else 0.
 // One workgroup per (row, segment), 16-byte copies (d * sizeof(T) is a multiple of 16).
 template <typename T>
-__global__ void relay_gather_kernel(int carry_on, const int* rec, const T* E, const T* f, int B, int d, int V, T* u,
+__global__ void relay_gather_kernel(int carry_on, const int* rec, const T* E, const T* f, int B, int d, int V,
                                     FragOut of) {
   const int row = blockIdx.x, seg = blockIdx.y;
   const int s = row / B, i = row - s * B;
   const int* r = rec + (size_t)s * CARRY_REC;
   const bool valid = carry_on && i >= 1 && i >= r[4] && i <= r[0] && r[0] < B && r[1] >= 1 &&
                      r[1] + r[0] <= B && r[2] >= 0 && r[2] < V && r[3] >= 0 && r[3] < V;
-  uint4* dst = reinterpret_cast<uint4*>(u + ((size_t)row * 3 + seg) * d);
   const int nvec = d * (int)sizeof(T) / 16;
   constexpr int EV = 16 / (int)sizeof(T);   // elements per 16-byte vector
   static_assert(EV == TT<T>::KL, "a 16-byte vector is one lane fragment");
@@ -358,31 +357,24 @@ __global__ void relay_gather_kernel(int carry_on, const int* rec, const T* E, co
     return reinterpret_cast<uint4*>(reinterpret_cast<T*>(of.p) + afrag_off<T>(row, of.c0 + seg * d + v * EV, of.ktiles));
   };
   if (!valid) {
-    for (int v = threadIdx.x; v < nvec; v += blockDim.x) {
-      dst[v] = make_uint4(0u, 0u, 0u, 0u);
-      if (of.p) *fdst(v) = make_uint4(0u, 0u, 0u, 0u);
-    }
+    for (int v = threadIdx.x; v < nvec; v += blockDim.x) *fdst(v) = make_uint4(0u, 0u, 0u, 0u);
     return;
   }
   const T* src = seg == 0 ? E + (size_t)r[2] * d : seg == 1 ? E + (size_t)r[3] * d
                                                             : f + ((size_t)s * B + r[1] + i - 1) * d;
   const uint4* sv = reinterpret_cast<const uint4*>(src);
-  for (int v = threadIdx.x; v < nvec; v += blockDim.x) {
-    const uint4 x = sv[v];
-    dst[v] = x;
-    if (of.p) *fdst(v) = x;
-  }
+  for (int v = threadIdx.x; v < nvec; v += blockDim.x) *fdst(v) = sv[v];
 }
 
 hipError_t launch_relay_gather(bool isbf, int carry_on, const int* carry_rec, const void* E, const void* f, int nseq,
-                               int B, int d, int V, void* u, FragOut of, hipStream_t s) {
-  if (d % 16) return hipErrorInvalidValue;
+                               int B, int d, int V, FragOut of, hipStream_t s) {
+  if (d % 16 || !of.p) return hipErrorInvalidValue;
   if (isbf)
     hipLaunchKernelGGL(relay_gather_kernel<bf16>, dim3(nseq * B, 3), dim3(256), 0, s, carry_on, carry_rec,
-                       (const bf16*)E, (const bf16*)f, B, d, V, (bf16*)u, of);
+                       (const bf16*)E, (const bf16*)f, B, d, V, of);
   else
     hipLaunchKernelGGL(relay_gather_kernel<float>, dim3(nseq * B, 3), dim3(256), 0, s, carry_on, carry_rec,
-                       (const float*)E, (const float*)f, B, d, V, (float*)u, of);
+                       (const float*)E, (const float*)f, B, d, V, of);
   return hipGetLastError();
 }
 

@@ -30,7 +30,7 @@ struct GemmParams {
   const void* A; int lda;           // activations [M, lda], storage type
   const void* W;                    // packed weight tiles of this column range
   int M, ntiles, ktiles;            // ntiles = N/16 of the range, ktiles = K/KT
-  void* Y; int ldy;
+  void* Y; int ldy;                 // null for EPI_SWIGLU and EPI_BIAS_SILU: only the copy yf is written
   const void* R; int ldr;
   void* Y2; int ldy2;
   const void* bias;

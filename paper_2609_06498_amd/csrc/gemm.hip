@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(512) gemm_kernel(GemmParams p) {
         up *= s_rs[m];
       }
       const float y = silu(gt) * up;
-      TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)m * p.ldy + obase + c, y);
+      if (p.Y) TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)m * p.ldy + obase + c, y);
       frag_st<T>(p.yf, m, obase + c, y);
     }
   } else {
@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(512) gemm_kernel(GemmParams p) {
         ct[m * CW + n] = v;
       } else if constexpr (EPI == EPI_BIAS_SILU) {
         v += x;
-        TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)m * p.ldy + col, silu(v));
+        if (p.Y) TT<T>::st(reinterpret_cast<T*>(p.Y), (size_t)m * p.ldy + col, silu(v));
         frag_st<T>(p.yf, m, col, silu(v));
       } else if constexpr (EPI == EPI_BIAS_F32) {
         v += x;

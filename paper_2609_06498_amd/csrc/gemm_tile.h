@@ -284,9 +284,11 @@ __global__ void __launch_bounds__(S::NW * 64, S::OCC * S::NW / 4) gemm_tile_kern
           *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.Y) + part + (size_t)m * p.ldy + col) =
               make_float4(v[0], v[1], v[2], v[3]);
         } else {
-          T* o = reinterpret_cast<T*>(p.Y) + (size_t)m * p.ldy + col;
-          pair_st<T>(o, v[0], v[1]);
-          pair_st<T>(o + 2, v[2], v[3]);
+          if (EPI != EPI_BIAS_SILU || p.Y) {
+            T* o = reinterpret_cast<T*>(p.Y) + (size_t)m * p.ldy + col;
+            pair_st<T>(o, v[0], v[1]);
+            pair_st<T>(o + 2, v[2], v[3]);
+          }
           if constexpr (EPI == EPI_BIAS_SILU) {
             if (p.yf.p) {
               T* f = reinterpret_cast<T*>(p.yf.p) + afrag_off<T>(m, p.yf.c0 + col, p.yf.ktiles);

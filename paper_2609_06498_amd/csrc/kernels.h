@@ -108,7 +108,7 @@ hipError_t launch_argmax_reduce(const uint64_t* amax, int groups, int M, uint64_
 hipError_t launch_accept(const int* block, const int* g, int nseq, int B, int carry_window, int* accept_len,
                          int* bonus, int* committed, int* n_carry, int* carry_rec, hipStream_t s);
 hipError_t launch_relay_gather(bool bf16, int carry_on, const int* carry_rec, const void* E, const void* f, int nseq,
-                               int B, int d, int V, void* u, FragOut of, hipStream_t s);
+                               int B, int d, int V, FragOut of, hipStream_t s);
 hipError_t launch_relay_input(bool bf16, int carry_on, const int* carry_rec, const int* anchor, const void* E,
                               const void* e_mask, const void* f, const float* bg, const void* ln_g,
                               const void* ln_b, float ln_eps, int nseq, int B, int d, int V, void* x, int* status,
