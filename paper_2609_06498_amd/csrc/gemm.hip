@@ -365,25 +365,33 @@ __global__ void __launch_bounds__(512) gemm_kernel(GemmParams p) {
 // Tile shapes of the many-row GEMM, and a launch's time by how the workgroups
 // fall on the compute units.  Measured on the Qwen3 projections (8 x 64 .. 64 x
 // 200 k tiles per workgroup, bf16): a workgroup's k tile takes t1 us when it has
-// its compute unit to itself and tn when the unit holds several.  The widest
-// tile reaches 1.17 PFLOP/s on full launches (8B gate/up at 1024 rows 176 us,
-// the register-staged 128 x 128 tile before it 245); the smaller ones are for
-// row counts and widths that would leave units idle (8B QKV at 128 rows 18.6 us
-// at 128 x 128, 15.5 at 128 x 64; 1.7B gate/up at 300 rows 29.7 us at 128 x
-// 128, 23.2 at 64 x 128).
+// its compute unit to itself and tn when the unit holds several, one after
+// another where the tile leaves no room for a second.
+// LDS reads bound full launches: a wave of 64 x 32 reads 6 KB per 8 matrix ops,
+// one of 64 x 64 8 KB per 16, so the widest tile takes 0.48 us a k tile for twice the
+// work of the 128 x 128 one's 0.28 (8B LM head at 512 rows 695 -> 617 us, gate/up
+// at 1024 rows 208 -> 190 us, 1.1 PFLOP/s) where it can fill the chip.  The
+// smaller ones are for row counts and widths that would leave units idle (8B
+// QKV at 128 rows 18.6 us at 128 x 128, 15.5 at 128 x 64; down at 1024 rows 107 us
+// at 128 x 128, 142 at 256 x 128).
 typedef TileShape<2, 4, 4, 2, 1, 2> Tile128x128;
 typedef TileShape<2, 2, 4, 2, 1, 3> Tile128x64;
 typedef TileShape<1, 4, 4, 2, 1, 3> Tile64x128;
 typedef TileShape<2, 2, 2, 2, 1, 4> Tile64x64;
+typedef TileShape<4, 2, 4, 4, 1, 1> Tile256x128;
 struct TileCost { int bm, bs; double t1, tn; };
-constexpr TileCost TILES[] = {{128, 8, 0.23, 0.23}, {128, 4, 0.18, 0.148}, {64, 8, 0.19, 0.146}, {64, 4, 0.15, 0.10}};
+constexpr TileCost TILES[] = {{128, 8, 0.26, 0.28}, {128, 4, 0.18, 0.165}, {64, 8, 0.19, 0.165}, {64, 4, 0.15, 0.115},
+                              {256, 8, 0.38, 0.48}};
 constexpr int N_TILES = sizeof(TILES) / sizeof(TILES[0]);
+// fp32 is bound by the matrix cores, not by LDS reads: no widest tile
+template <typename T> constexpr int tiles_of() { return sizeof(T) == 2 ? N_TILES : N_TILES - 1; }
 
 // the fastest tile for M rows x ntiles strips x ktiles in ks K parts, and its time in us
+template <typename T>
 static int pick_tile(int M, int ntiles, int ktiles, int ks, int cus, double* us) {
   int best = 0;
   double tb = 1e30;
-  for (int i = 0; i < N_TILES; ++i) {
+  for (int i = 0; i < tiles_of<T>(); ++i) {
     const TileCost& c = TILES[i];
     const long long wgs = (long long)((M + c.bm - 1) / c.bm) * ((ntiles + c.bs - 1) / c.bs) * ks;
     const long long n = (wgs + cus - 1) / cus;
@@ -416,7 +424,10 @@ template <typename T, int EPI>
 static hipError_t launch_tile(const GemmParams& p, int waves, int ks, hipStream_t st) {
   if (!p.Af || (p.norm && !p.rs)) return hipErrorInvalidValue;
   double us;
-  switch (pick_tile(p.M, p.ntiles, p.ktiles, ks, p.cus > 0 ? p.cus : 256, &us)) {
+  const int tile = pick_tile<T>(p.M, p.ntiles, p.ktiles, ks, p.cus > 0 ? p.cus : 256, &us);
+  if constexpr (tiles_of<T>() > 4)
+    if (tile == 4) return launch_tile_shape<T, EPI, Tile256x128>(p, waves, ks, st);
+  switch (tile) {
     case 0: return launch_tile_shape<T, EPI, Tile128x128>(p, waves, ks, st);
     case 1: return launch_tile_shape<T, EPI, Tile128x64>(p, waves, ks, st);
     case 2: return launch_tile_shape<T, EPI, Tile64x128>(p, waves, ks, st);
@@ -633,13 +644,14 @@ __global__ void __launch_bounds__(256) range_reduce_kernel(GemmParams p, const f
 // reduce kernel), whichever is estimated faster.  A reduce takes about 4 us
 // plus its bytes at 6.5 TB/s (measured: four parts of 128 x 4096 5 us, of 1024
 // x 4096 14.7 us), and so do the partial sums' writes.
+template <typename T>
 static int tile_parts(int epi, const GemmParams& p) {
   const int nw = split_parts(epi, p.ntiles, p.ktiles);
   if (nw < 2 || !p.part_ws || (epi != EPI_RESID && p.M > split_max_rows(epi))) return 1;
   const int cus = p.cus > 0 ? p.cus : 256;
   double whole, split;
-  pick_tile(p.M, p.ntiles, p.ktiles, 1, cus, &whole);
-  pick_tile(p.M, p.ntiles, p.ktiles, nw, cus, &split);
+  pick_tile<T>(p.M, p.ntiles, p.ktiles, 1, cus, &whole);
+  pick_tile<T>(p.M, p.ntiles, p.ktiles, nw, cus, &split);
   const double part_us = (double)p.M * p.ntiles * 16 * 4 / 6.5e6;   // one part's sums, once over memory
   const double fold1 = epi == EPI_RESID ? 4.0 + 2.0 * part_us : 0.0;
   return split + 4.0 + 2.0 * nw * part_us < whole + fold1 ? nw : 1;
@@ -684,7 +696,7 @@ static hipError_t launch_many(int epi, const GemmParams& p, hipStream_t st) {
   const int ks = p.ksplit > 1 ? p.ksplit : 1;
   const int waves = gemm_shape(p.ntiles, p.ktiles, epi, ks).waves;
   if (ks > 1) return epi == EPI_STORE_F32 ? launch_tile<T, EPI_STORE_F32>(p, waves, ks, st) : hipErrorInvalidValue;
-  const int parts = epi == EPI_ARGMAX ? 1 : tile_parts(epi, p);
+  const int parts = epi == EPI_ARGMAX ? 1 : tile_parts<T>(epi, p);
   GemmParams q;
   hipError_t e;
   if (epi == EPI_RESID) {
