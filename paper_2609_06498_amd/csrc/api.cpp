@@ -76,6 +76,7 @@ struct dflow_ctx {
   void* samp;            // sampling decoding partials
   float* samp_row;       // [vocab] logits of the last prompt row (dflow_prefill_sampled)
   float* rs;             // [mmax] RMSNorm row scales of x (launches of more than SPLIT_MIN_ROWS rows)
+  unsigned* arrive;      // arrival counters of the residual GEMMs; every launch leaves them at 0
   float* kpart;          // K-part partial sums of the split residual and gate/up GEMMs
   // Matrix-core-order copies of the projections' A operands (mmax rows,
   // rounded up to 16): x (QKV, gate/up, LM heads), attention output (O), SwiGLU
@@ -231,6 +232,7 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* lm_groups_out) {
     add(fr * d->d);                                       // 32 projected features
   }
   add((size_t)mmax * 4);                                  // 33 rs: RMSNorm row scales
+  add(MAX_ROWS / 64 * 4);                                 // 34 arrival counters of the residual GEMMs (zero between launches)
   L.total = o;
   if (nsplit_out) *nsplit_out = nsplit;
   if (lm_groups_out) *lm_groups_out = lm_groups;
@@ -336,6 +338,7 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   c->uf = b + L.off[31];
   c->ff = b + L.off[32];
   c->rs = (float*)(b + L.off[33]);
+  c->arrive = (unsigned*)(b + L.off[34]);
 
   // RoPE table: angle p * theta^(-2i/Dh) evaluated in double
   const int half = dims->head_dim / 2;
@@ -418,6 +421,7 @@ hipError_t gemm(dflow_ctx* c, hipStream_t st, int epi, const void* A, int lda, c
   }
   p.eps = c->dm.rms_eps;
   p.rs_out = c->rs;
+  p.arrive = c->arrive;
   p.ssq_out = ssq_out;
   p.ssq_out_ld = SSQ_LD;
   p.A = A;

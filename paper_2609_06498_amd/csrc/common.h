@@ -137,6 +137,26 @@ __device__ inline void frag_st4(const FragOut& f, int m, int c, const float* v) 
   else *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
+template <typename T> struct Run4;   // four consecutive values <-> fp32
+template <> struct Run4<float> {
+  __device__ static inline void load(const float* p, float* v) {
+    const float4 u = *reinterpret_cast<const float4*>(p);
+    v[0] = u.x; v[1] = u.y; v[2] = u.z; v[3] = u.w;
+  }
+  __device__ static inline void store(float* p, const float* v) {
+    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  }
+};
+template <> struct Run4<bf16> {
+  __device__ static inline void load(const bf16* p, float* v) {
+    const uint2 u = *reinterpret_cast<const uint2*>(p);
+    v[0] = bf2f(u.x & 0xFFFF); v[1] = bf2f(u.x >> 16); v[2] = bf2f(u.y & 0xFFFF); v[3] = bf2f(u.y >> 16);
+  }
+  __device__ static inline void store(bf16* p, const float* v) {
+    *reinterpret_cast<uint2*>(p) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+  }
+};
+
 template <typename T> struct Row16;
 template <> struct Row16<bf16> {
   __device__ static inline void load(const bf16* p, float* v) {
@@ -246,6 +266,18 @@ __device__ inline float block_sum(float v, float* sh /* >= 32 floats */) {
   float s = 0.f;
   for (int i = 0; i < nw; ++i) s += sh[i];
   return s;
+}
+
+// Sum of squares of a 16-column strip, in column order with fused operations:
+// sq_start of columns 0 and 1, then sq_next.  Written out, because fp32 row
+// scales are only equal bit for bit across the kernels that compute them if all round alike.
+__device__ inline float sq_start(float a, float b) { return fmaf(a, a, b * b); }
+__device__ inline float sq_next(float sq, float a) { return fmaf(a, a, sq); }
+__device__ inline float strip_sq(const float* v) {
+  float sq = sq_start(v[0], v[1]);
+#pragma unroll
+  for (int c = 2; c < 16; ++c) sq = sq_next(sq, v[c]);
+  return sq;
 }
 
 // RMSNorm row scale (sum_c sq[c] / (16 np) + eps)^(-1/2) from a row's per-strip

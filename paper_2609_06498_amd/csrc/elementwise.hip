@@ -21,15 +21,14 @@ __global__ void embed_kernel(const int* tok, const T* E, int V, int d, T* out, i
   const bool ok = t >= 0 && t < V;
   if (!ok && threadIdx.x == 0) set_status(status, ST_BAD_TOKEN);
   for (int c = threadIdx.x; c < d / 16; c += blockDim.x) {
-    float sq = 0.f, vs[16];
+    float vs[16];
     if (ok) {
       Row16<T>::load(E + (size_t)t * d + (size_t)c * 16, vs);
     } else {
 #pragma unroll
       for (int e = 0; e < 16; ++e) vs[e] = 0.f;
     }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) sq += vs[e] * vs[e];
+    const float sq = strip_sq(vs);
     Row16<T>::store(out + (size_t)row * d + (size_t)c * 16, vs);
     frag_st_run<T>(of, row, c * 16, vs, 16);
     ssq[(size_t)row * ssq_ld + c] = sq;
@@ -153,26 +152,6 @@ hipError_t launch_rmsnorm(bool isbf, bool in_f32, const void* x, int ldx, int M,
 // together, because their keys and values share the cache lines of a page.
 // Bound by memory traffic; one wave per (row, head) with 4-byte accesses
 // took 20.8 us for 1024 rows of the Qwen3-8B shape, 9.7 us for 512 of the 1.7B shape.
-template <typename T> struct Run4;   // four consecutive values <-> fp32
-template <> struct Run4<float> {
-  __device__ static inline void load(const float* p, float* v) {
-    const float4 u = *reinterpret_cast<const float4*>(p);
-    v[0] = u.x; v[1] = u.y; v[2] = u.z; v[3] = u.w;
-  }
-  __device__ static inline void store(float* p, const float* v) {
-    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-  }
-};
-template <> struct Run4<bf16> {
-  __device__ static inline void load(const bf16* p, float* v) {
-    const uint2 u = *reinterpret_cast<const uint2*>(p);
-    v[0] = bf2f(u.x & 0xFFFF); v[1] = bf2f(u.x >> 16); v[2] = bf2f(u.y & 0xFFFF); v[3] = bf2f(u.y >> 16);
-  }
-  __device__ static inline void store(bf16* p, const float* v) {
-    *reinterpret_cast<uint2*>(p) = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
-  }
-};
-
 template <typename T, int DH>
 __global__ void __launch_bounds__(256) qk_rope_kernel(RopeParams p) {
   constexpr int LPR = DH / 8, HALF = DH / 2;
@@ -518,9 +497,7 @@ __global__ void __launch_bounds__(256) relay_input_kernel(int carry_on, const in
     }
     Row16<T>::store(xr + (size_t)c * 16, v);
     frag_st_run<T>(of, row, c * 16, v, 16);
-    float sq = 0.f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) sq += v[e] * v[e];
+    const float sq = strip_sq(v);
     ssq[(size_t)row * ssq_ld + c] = sq;
     s_sq[c] = sq;
   }

@@ -51,8 +51,9 @@ struct GemmParams {
   // sums at Y + h * y_part (floats), and the consumer adds the parts
   int ksplit; size_t y_part;
   float* rs_out;     // EPI_RESID above SPLIT_MIN_ROWS rows: [M] RMSNorm scales of the stored rows (for d = N)
+  unsigned* arrive;  // EPI_RESID above SPLIT_MIN_ROWS rows: a counter per 64 rows, zero between launches
   // above SPLIT_MIN_ROWS rows: fp32 scratch of split_parts(epi, ntiles,
-  // ktiles) x M x N floats for K-part partial sums (EPI_RESID always; the
+  // ktiles) x M x N floats for K-part partial sums (EPI_RESID at any M, the
   // others up to split_max_rows(epi) rows; null: no split)
   float* part_ws;
   int cus;                          // compute units (0: unknown, no balance-driven split)

@@ -348,13 +348,7 @@ __global__ void __launch_bounds__(512) gemm_kernel(GemmParams p) {
         __syncthreads();
         for (int e = threadIdx.x; e < M * nvalid; e += blockDim.x) {
           const int m = e / nvalid, j = e - m * nvalid;
-          float sq = 0.f;
-#pragma unroll
-          for (int c = 0; c < 16; ++c) {
-            const float v = ct[m * CW + j * 16 + c];
-            sq += v * v;
-          }
-          p.ssq_out[(size_t)m * p.ssq_out_ld + nt0 + j] = sq;
+          p.ssq_out[(size_t)m * p.ssq_out_ld + nt0 + j] = strip_sq(ct + m * CW + j * 16);
         }
       }
     }
@@ -544,12 +538,9 @@ __global__ void __launch_bounds__(256) resid_reduce_kernel(const float* part, si
     float r[16], s[16];
     Row16<T>::load(R + (size_t)m * ldr + j * 16, r);
     sum_parts16<KS>(part, part_stride, ks, (size_t)m * N + j * 16, s);
-    float sq = 0.f;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) {
-      s[c] = TT<T>::rnd(s[c] + r[c]);
-      sq += s[c] * s[c];
-    }
+    for (int c = 0; c < 16; ++c) s[c] = TT<T>::rnd(s[c] + r[c]);
+    const float sq = strip_sq(s);
     Row16<T>::store(Y + (size_t)m * ldy + j * 16, s);
     if (Y2) Row16<T>::store(Y2 + (size_t)m * ldy2 + j * 16, s);
     frag_st_run<T>(yf, m, j * 16, s, 16);
@@ -643,7 +634,8 @@ __global__ void __launch_bounds__(256) range_reduce_kernel(GemmParams p, const f
 // compute units idle, one per range (fp32 partial sums to part_ws, folded by a
 // reduce kernel), whichever is estimated faster.  A reduce takes about 4 us
 // plus its bytes at 6.5 TB/s (measured: four parts of 128 x 4096 5 us, of 1024
-// x 4096 14.7 us), and so do the partial sums' writes.
+// x 4096 14.7 us), and so do the partial sums' writes; the row scales of a
+// whole residual launch add about 3 us.
 template <typename T>
 static int tile_parts(int epi, const GemmParams& p) {
   const int nw = split_parts(epi, p.ntiles, p.ktiles);
@@ -653,7 +645,7 @@ static int tile_parts(int epi, const GemmParams& p) {
   pick_tile<T>(p.M, p.ntiles, p.ktiles, 1, cus, &whole);
   pick_tile<T>(p.M, p.ntiles, p.ktiles, nw, cus, &split);
   const double part_us = (double)p.M * p.ntiles * 16 * 4 / 6.5e6;   // one part's sums, once over memory
-  const double fold1 = epi == EPI_RESID ? 4.0 + 2.0 * part_us : 0.0;
+  const double fold1 = epi == EPI_RESID ? 3.0 : 0.0;
   return split + 4.0 + 2.0 * nw * part_us < whole + fold1 ? nw : 1;
 }
 
@@ -672,10 +664,9 @@ static hipError_t launch_parts(const GemmParams& p, int waves, int ks, GemmParam
   return launch_tile<T, EPI_STORE_F32>(q, waves, ks, st);
 }
 
-// the part count as a template argument where it is one or a wave count, so all loads are in flight at once
+// the part count as a template argument where it is a wave count, so all loads are in flight at once
 template <typename F>
 static hipError_t with_parts(int ks, F&& go) {
-  if (ks == 1) return go(std::integral_constant<int, 1>{});
   if (ks == 2) return go(std::integral_constant<int, 2>{});
   if (ks == 4) return go(std::integral_constant<int, 4>{});
   if (ks == 8) return go(std::integral_constant<int, 8>{});
@@ -700,9 +691,9 @@ static hipError_t launch_many(int epi, const GemmParams& p, hipStream_t st) {
   GemmParams q;
   hipError_t e;
   if (epi == EPI_RESID) {
-    // the whole row's scale goes with the residual epilogue, so it always runs on the folded sums
-    if (p.norm || p.col0 || !p.part_ws || !p.ssq_out || !p.rs_out) return hipErrorInvalidValue;
-    if ((e = launch_parts<T>(p, parts > 1 ? 1 : waves, parts, &q, st)) != hipSuccess) return e;
+    if (p.norm || p.col0 || !p.ssq_out || !p.rs_out || !p.arrive) return hipErrorInvalidValue;
+    if (parts == 1) return launch_tile<T, EPI_RESID>(p, waves, 1, st);
+    if ((e = launch_parts<T>(p, 1, parts, &q, st)) != hipSuccess) return e;
     const int threads = p.ntiles < 256 ? (p.ntiles + 63) / 64 * 64 : 256;
     return with_parts(parts, [&](auto k) {
       hipLaunchKernelGGL((resid_reduce_kernel<T, decltype(k)::value>), dim3(p.M), dim3(threads), 0, st, p.part_ws,

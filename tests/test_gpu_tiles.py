@@ -25,7 +25,10 @@ DIMS = {
     # 3, 4 and 5 k tiles per projection, 17 strips of vocabulary
     "bf16-narrow": ModelDims("bf16", 96, 2, 2, 1, 64, 160, 272, 1, (0, 1)),
     "f32-narrow": ModelDims("f32", 48, 2, 2, 1, 64, 112, 272, 1, (0, 1)),
+    # gate/up of 257 column tiles: 256-row tiles at 1000 and 1024 rows
+    "bf16-wide": ModelDims("bf16", 256, 2, 4, 2, 64, 16416, 272, 1, (0, 1)),
 }
+ROWS = (48, 49, 64, 65, 127, 129, 200, 256, 257, 384, 512, 513, 1024)
 
 
 @pytest.mark.parametrize("name", sorted(DIMS))
@@ -39,7 +42,7 @@ def test_chunk_rows_bitwise(name):
     tok = torch.from_numpy(np.concatenate(prompts)).cuda()
     w = make_weights(dims, 11)
     ref = None
-    for rows in (48, 49, 64, 65, 127, 129, 200, 256, 257, 384, 512, 513, 1024):
+    for rows in (48, 512, 1000, 1024) if name == "bf16-wide" else ROWS:
         print(f"[tiles] {name} rows={rows}", flush=True)
         rt = Runtime(dims, 16, 2, 2400, w, max_rows=rows)
         first = torch.zeros(2, dtype=torch.int32, device="cuda")
