@@ -39,6 +39,10 @@ int fail(int code, const char* fmt, ...) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 }  // namespace
 
+// Rows of a prefill chunk that belong to one sequence: chunk rows row0 ..
+// row0 + n - 1 are its positions pos0 .. pos0 + n - 1.
+struct Seg { int seq, row0, n, pos0; };
+
 struct dflow_ctx {
   dflow_dims dm;
   bool bf;
@@ -55,19 +59,19 @@ struct dflow_ctx {
 
   dflow_weights w;
   std::vector<dflow_layer> layers, dlayers;
+  std::vector<Seg> segs;     // of the prefill chunk being issued (room for max_batch from the start)
   dflow_cache c;
   size_t pool_layer_elems;   // elements of one layer pool (K or V)
 
   void* ws = nullptr;         // caller-owned workspace (dflow_workspace_bytes)
   size_t ws_bytes = 0;
-  int prefill_keys = 0;            // keys up to the end of the prefill chunk being issued (host plan)
   int phase = DFLOW_PHASE_OTHER;   // entry point being issued (tags the kernel-timing record)
   // workspace views
   void *x, *qkv, *q, *hcap, *f;
   float *fproj, *bg, *part_o, *part_ml;
   float2* rope;
   uint64_t* amax;
-  int *carry_rec, *status, *tmp_pos, *tmp_argmax;
+  int *carry_rec, *status, *tmp_pos;
   float* ssq;   // [mmax][SSQ_LD] sums of squares of x per 16-column strip (RMSNorm row scales)
   uint64_t* amax_part;   // [ARGMAX_SPLITS][mmax]
   unsigned* counters;    // arrival counters of last-workgroup reductions; every launch leaves them at 0
@@ -198,7 +202,7 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* lm_groups_out) {
   add((size_t)d->max_batch * CARRY_REC * 4);           // 15 carry_rec
   add(4);                                              // 16 unused (the status word is the caller's)
   add((size_t)(d->max_batch + 1) * 4);                 // 17 tmp_pos
-  add((size_t)mmax * 4);                               // 18 tmp_argmax
+  add(0);                                              // 18 unused
   add((size_t)mmax * SSQ_LD * 4);                      // 19 ssq: per-strip sums of squares of the residual rows
   add((size_t)ARGMAX_SPLITS * mmax * 8);               // 20 amax_part: [split][row] partial argmax keys
   add(ARGMAX_BLOCKS * 4);                              // 21 counters (zero between launches)
@@ -296,6 +300,7 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   }
   c->w = *w;
   c->layers.assign(w->layers, w->layers + dims->n_layers);
+  c->segs.reserve(dims->max_batch);
   c->dlayers.assign(w->draft_layers, w->draft_layers + dims->n_draft_layers);
   c->w.layers = c->layers.data();
   c->w.draft_layers = c->dlayers.data();
@@ -322,7 +327,6 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   c->carry_rec = (int*)(b + L.off[15]);
   c->status = status;
   c->tmp_pos = (int*)(b + L.off[17]);
-  c->tmp_argmax = (int*)(b + L.off[18]);
   c->ssq = (float*)(b + L.off[19]);
   c->amax_part = (uint64_t*)(b + L.off[20]);
   c->counters = (unsigned*)(b + L.off[21]);
@@ -464,15 +468,17 @@ hipError_t gemm(dflow_ctx* c, hipStream_t st, int epi, const void* A, int lda, c
 
 void* pool_layer(dflow_ctx* c, void* pool, int l) { return (char*)pool + (size_t)l * c->pool_layer_elems * c->elt; }
 
-// Attention of `nseq` sequences x Bq rows over one layer's pools.  Prefill has
+// Attention of `nseq` sequences x Bq rows over one layer's pools.  Prefill (seg:
+// that segment's rows, nseq = 1, Bq = its length) has
 // a kernel of its own (from c->q, keys and values already cached).  With
 // `fused`, from the raw QKV projection rows (QK-norm, RoPE and the block's
 // KV-cache write happen inside); otherwise from c->q after qk_rope.
 hipError_t attention(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int nseq, int Bq, const int* start_pos,
-                     const int* page_table, void* kpool, void* vpool, int causal, bool fused) {
+                     const int* page_table, void* kpool, void* vpool, int causal, bool fused, const Seg* seg) {
   AttnParams a{};
   a.fused = fused ? 1 : 0;
-  a.q = c->q;
+  a.q = (char*)c->q + (seg ? (size_t)seg->row0 * c->q_dim * c->elt : 0);
+  a.out_row0 = seg ? seg->row0 : 0;
   a.qkv = reinterpret_cast<const float*>(c->qkv);
   a.ld_qkv = c->qkv_n;
   a.qkv_ks = c->qkv_ks;
@@ -493,10 +499,9 @@ hipError_t attention(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int nse
   a.Hkv = c->dm.n_kv_heads;
   a.Dh = c->dm.head_dim;
   a.causal = causal;
-  const bool prefill = c->phase == DFLOW_PHASE_PREFILL;
-  if (prefill) {
+  if (seg) {
     a.split_keys = PREFILL_SPLIT;
-    a.nsplit = (c->prefill_keys + PREFILL_SPLIT - 1) / PREFILL_SPLIT;
+    a.nsplit = (seg->pos0 + seg->n + PREFILL_SPLIT - 1) / PREFILL_SPLIT;
     a.row_splits = 1;
   } else {
     const int nw = attention_waves(fused, Bq, c->G), nrg = (Bq * c->G + 15) / 16;
@@ -511,7 +516,7 @@ hipError_t attention(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int nse
   // per prefetched byte (8B shape, same box: O 4.400 -> 4.377 ms/round,
   // gate/up 4.392 -> 4.359; 1.7B shape: O 1.932 -> 1.897, gate/up 1.898 ->
   // 1.917, its shorter attention stretched by the larger prefetch).
-  if (!prefill && L.wo && L.wgu && c->cus > nseq * a.Hkv * a.nsplit) {
+  if (!seg && L.wo && L.wgu && c->cus > nseq * a.Hkv * a.nsplit) {
     const int idle = c->cus - nseq * a.Hkv * a.nsplit;
     const size_t cap = (size_t)idle * ATTN_PF_WG_BYTES;
     const size_t wo_bytes = (size_t)c->dm.d * c->q_dim * c->elt;
@@ -530,7 +535,7 @@ hipError_t attention(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int nse
   const bool rec = c->prof && c->n_ev < PROF_MAX;
   hipError_t e;
   if (rec && (e = hipEventRecord(c->ev0[c->n_ev], st)) != hipSuccess) return e;
-  if ((e = prefill ? launch_attention_prefill(c->bf, a, c->cus, st) : launch_attention(c->bf, a, st)) != hipSuccess)
+  if ((e = seg ? launch_attention_prefill(c->bf, a, c->cus, st) : launch_attention(c->bf, a, st)) != hipSuccess)
     return e;
   if (rec) {
     if ((e = hipEventRecord(c->ev1[c->n_ev], st)) != hipSuccess) return e;
@@ -565,10 +570,12 @@ RopeParams rope_params(dflow_ctx* c, const dflow_layer& L, int nseq, int Bq, int
   return r;
 }
 
-// One Qwen3-style decoder layer over x (M = nseq*Bq rows) in place.
+// One Qwen3-style decoder layer over x (M = nseq*Bq rows) in place.  Prefill:
+// nseq = 1, Bq = the chunk's rows and their segments; a segment's position is
+// in c->tmp_pos[seq].
 hipError_t decoder_layer(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int nseq, int Bq, const int* start_pos,
                          const int* page_table, void* kpool, void* vpool, int causal, void* capture,
-                         FragOut capf = FragOut{nullptr, 0, 0}) {
+                         FragOut capf = FragOut{nullptr, 0, 0}, const std::vector<Seg>* segs = nullptr) {
   const dflow_dims& d = c->dm;
   const int M = nseq * Bq;
   hipError_t e;
@@ -598,15 +605,22 @@ hipError_t decoder_layer(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int
   if ((e = gemm(c, st, EPI_STORE_F32, c->x, d.d, L.wqkv, M, c->qkv_n, d.d, c->qkv, c->qkv_n, nullptr, 0, nullptr, 0,
                 nullptr, nullptr, 0, attn_n, nullptr, c->qkv_ks, fq)))
     return e;
-  const bool fused = c->phase != DFLOW_PHASE_PREFILL && attention_fuses_rope(c->bf, Bq, c->G, d.head_dim, c->split_keys);
-  if (!fused) {
-    RopeParams r = rope_params(c, L, nseq, Bq, d.n_heads, start_pos, nullptr, page_table, kpool, vpool);
-    r.qkv32 = reinterpret_cast<const float*>(c->qkv);
-    r.ld = c->qkv_n;
-    r.part = c->qkv_ks == 2 ? (size_t)M * c->qkv_n : 0;
-    if ((e = launch_qk_rope_write(c->bf, r, st))) return e;
+  const bool fused = !segs && attention_fuses_rope(c->bf, Bq, c->G, d.head_dim, c->split_keys);
+  for (size_t i = 0; i < (segs ? segs->size() : 1); ++i) {
+    const Seg* sg = segs ? &(*segs)[i] : nullptr;
+    const int rows = sg ? sg->n : Bq;
+    const int* pos = sg ? c->tmp_pos + sg->seq : start_pos;
+    const int* pt = sg ? c->c.page_table + (size_t)sg->seq * d.max_pages : page_table;
+    if (!fused) {
+      RopeParams r = rope_params(c, L, nseq, rows, d.n_heads, pos, nullptr, pt, kpool, vpool);
+      r.qkv32 = reinterpret_cast<const float*>(c->qkv) + (sg ? (size_t)sg->row0 * c->qkv_n : 0);
+      if (sg) r.q_out = (char*)c->q + (size_t)sg->row0 * c->q_dim * c->elt;
+      r.ld = c->qkv_n;
+      r.part = c->qkv_ks == 2 ? (size_t)M * c->qkv_n : 0;
+      if ((e = launch_qk_rope_write(c->bf, r, st))) return e;
+    }
+    if ((e = attention(c, st, L, nseq, rows, pos, pt, kpool, vpool, causal, fused, sg))) return e;
   }
-  if ((e = attention(c, st, L, nseq, Bq, start_pos, page_table, kpool, vpool, causal, fused))) return e;
   if ((e = gemm(c, st, EPI_RESID, nullptr, c->q_dim, L.wo, M, d.d, c->q_dim, c->x, d.d, c->x, d.d, nullptr, 0,
                 nullptr, nullptr, 0, NormIn(), c->ssq, 1, fo)))
     return e;
@@ -620,14 +634,12 @@ hipError_t decoder_layer(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int
   return hipSuccess;
 }
 
-// Target forward over block rows already embedded in x; argmax of every row
-// into `argmax_out`.  The captured states go to the matrix-core-order operand
+// Target layers over rows already embedded in x (segs: a prefill chunk's
+// segments).  The captured states go to the matrix-core-order operand
 // of W_c, and with `rows_out` to the row-major c->hcap too.
-hipError_t target_forward(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const int* start_pos,
-                          const int* page_table, int* argmax_out, float* logits, bool rows_out, int lm_row0 = 0,
-                          int lm_rows = -1) {
+hipError_t target_layers(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const int* start_pos,
+                         const int* page_table, bool rows_out, const std::vector<Seg>* segs) {
   const dflow_dims& d = c->dm;
-  const int M = nseq * Bq;
   hipError_t e;
   int ci = 0;
   for (int l = 0; l < d.n_layers; ++l) {
@@ -639,12 +651,17 @@ hipError_t target_forward(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const 
       ++ci;
     }
     if ((e = decoder_layer(c, st, c->layers[l], nseq, Bq, start_pos, page_table, pool_layer(c, c->c.k_pool, l),
-                           pool_layer(c, c->c.v_pool, l), 1, cap, capf)))
+                           pool_layer(c, c->c.v_pool, l), 1, cap, capf, segs)))
       return e;
   }
+  return hipSuccess;
+}
+
+// LM head (final RMSNorm folded in) over rows row0 .. row0 + rows - 1 of x: argmax of each into argmax_out, logits
+hipError_t target_head(dflow_ctx* c, hipStream_t st, int lm_row0, int lm_rows, int* argmax_out, float* logits) {
+  const dflow_dims& d = c->dm;
+  hipError_t e;
   if (!argmax_out && !logits) return hipSuccess;
-  // LM head (final RMSNorm folded in) over rows lm_row0 .. lm_row0+lm_rows-1 only
-  if (lm_rows < 0) lm_rows = M;
   const size_t off = (size_t)lm_row0 * d.d * c->elt;
   NormIn fin;
   fin.ssq = c->ssq + (size_t)lm_row0 * SSQ_LD;
@@ -675,7 +692,7 @@ hipError_t project(dflow_ctx* c, hipStream_t st, int M, void* out) {
 // All drafter layers at once: one GEMM over the stacked [Wk; Wv] of every
 // layer, then K-norm + RoPE + paged write for every layer in one launch.
 hipError_t ctx_append(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const int* start_pos,
-                      const int* row_limit, const int* page_table) {
+                      const int* row_limit, const int* page_table, const std::vector<Seg>* segs = nullptr) {
   const dflow_dims& d = c->dm;
   if (d.n_draft_layers < 1) return hipSuccess;
   const int M = nseq * Bq;
@@ -708,7 +725,15 @@ hipError_t ctx_append(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const int*
   r.layer_cols = 2 * c->kv_dim;
   r.pool_stride = c->pool_layer_elems;
   r.k_norms = c->dknorm;
-  return launch_qk_rope_write(c->bf, r, st);
+  if (!segs) return launch_qk_rope_write(c->bf, r, st);
+  for (const Seg& sg : *segs) {
+    r.qkv = (char*)c->ctxkv + (size_t)sg.row0 * ncols * c->elt;
+    r.M = r.Bq = sg.n;
+    r.start_pos = c->tmp_pos + sg.seq;
+    r.page_table = c->c.page_table + (size_t)sg.seq * d.max_pages;
+    if ((e = launch_qk_rope_write(c->bf, r, st))) return e;
+  }
+  return hipSuccess;
 }
 
 int check_nseq(dflow_ctx* c, int nseq) {
@@ -722,43 +747,64 @@ int check_nseq(dflow_ctx* c, int nseq) {
 namespace {
 int sampler_args(const dflow_ctx* c, const dflow_sampler* smp, const int32_t* pos, SampleArgs* a);
 
-// Prompt processing in chunks of max_rows; the last chunk's final row gives
-// the first token: its argmax, or a draw at temperature T when smp is given.
-int prefill_impl(dflow_ctx* c, hipStream_t st, int seq, const int32_t* tok, int len, const dflow_sampler* smp,
-                 int32_t* first) {
+// Prompts of sequences seq .. seq + nseq - 1, one after another in tok, in
+// chunks of max_rows rows of that row stream: short prompts and the ends of
+// long ones share a chunk, whose projections run once for all its sequences
+// (attention and cache writes per sequence; a row's arithmetic does not depend
+// on its chunk).  A prompt's last row gives its first token: its argmax, or a
+// draw at temperature T when smp is given (one sequence).  Six prompts of 20
+// .. 900 tokens on the 1.7B shape, 512-row chunks: one prompt at a time took 9
+// to 10 chunks and 2.8 ms for two layers, together 6 to 7 and 2.0 ms.
+int prefill_impl(dflow_ctx* c, hipStream_t st, int seq, int nseq, const int32_t* tok, const int32_t* len,
+                 const dflow_sampler* smp, int32_t* first) {
   if (!c || !tok || !first) return fail(DFLOW_EINVAL, "prefill: null argument");
-  if (seq < 0 || seq >= c->dm.max_batch) return fail(DFLOW_EINVAL, "prefill: seq %d", seq);
-  if (len < 1) return fail(DFLOW_ESHAPE, "prefill: len %d", len);
-  if ((long long)len + c->dm.block > (long long)c->dm.max_pages * PAGE)
-    return fail(DFLOW_ECAPACITY, "prefill: %d tokens exceed the page table (%d)", len, c->dm.max_pages * PAGE);
+  if (seq < 0 || seq + nseq > c->dm.max_batch) return fail(DFLOW_EINVAL, "prefill: seq %d", seq);
+  for (int i = 0; i < nseq; ++i) {   // every length is checked before anything is launched
+    if (len[i] < 1) return fail(DFLOW_ESHAPE, "prefill: sequence %d has %d tokens", seq + i, len[i]);
+    if ((long long)len[i] + c->dm.block > (long long)c->dm.max_pages * PAGE)
+      return fail(DFLOW_ECAPACITY, "prefill: sequence %d: %d tokens exceed the page table (%d)", seq + i, len[i],
+                  c->dm.max_pages * PAGE);
+  }
   c->phase = DFLOW_PHASE_PREFILL;
   SampleArgs sa;
   if (smp) {
-    // counter word 0 of the first draw: the prompt's last position (held in tmp_pos[1])
-    int rc = sampler_args(c, smp, c->tmp_pos + 1, &sa);
+    // counter word 0 of the first draw: the prompt's last position (held in tmp_pos[max_batch])
+    int rc = sampler_args(c, smp, c->tmp_pos + c->dm.max_batch, &sa);
     if (rc) return rc;
   }
   const dflow_dims& d = c->dm;
-  const int* pt = c->c.page_table + (size_t)seq * d.max_pages;
-  for (int p0 = 0; p0 < len; p0 += d.max_rows) {
-    const int n = (len - p0) < d.max_rows ? (len - p0) : d.max_rows;
-    const bool last = p0 + n >= len;
-    c->prefill_keys = p0 + n;
-    HIPCHK(launch_set_int(c->tmp_pos, p0, st));
-    HIPCHK(launch_embed(c->bf, tok + p0, n, c->w.embed, d.vocab, d.d, c->x, c->status, c->ssq, SSQ_LD,
-                        c->rs, d.rms_eps, fout(c, c->xf, d.d), st));
-    int* amax = last && !smp ? c->tmp_argmax : nullptr;
-    float* lrow = last && smp ? c->samp_row : nullptr;
-    HIPCHK(target_forward(c, st, 1, n, c->tmp_pos, pt, amax, lrow, false, n - 1, 1));
+  std::vector<Seg>& segs = c->segs;
+  const int32_t* t = tok;
+  for (int s = 0, p = 0; s < nseq;) {          // prompt s from its position p on
+    int n = 0;
+    segs.clear();
+    while (s < nseq && n < d.max_rows) {
+      const int take = len[s] - p < d.max_rows - n ? len[s] - p : d.max_rows - n;
+      segs.push_back(Seg{seq + s, n, take, p});
+      HIPCHK(launch_set_int(c->tmp_pos + seq + s, p, st));
+      n += take;
+      p += take;
+      if (p == len[s]) {
+        ++s;
+        p = 0;
+      }
+    }
+    HIPCHK(launch_embed(c->bf, t, n, c->w.embed, d.vocab, d.d, c->x, c->status, c->ssq, SSQ_LD, c->rs, d.rms_eps,
+                        fout(c, c->xf, d.d), st));
+    t += n;
+    HIPCHK(target_layers(c, st, 1, n, nullptr, nullptr, false, &segs));
+    for (const Seg& sg : segs)
+      if (sg.pos0 + sg.n == len[sg.seq - seq])
+        HIPCHK(target_head(c, st, sg.row0 + sg.n - 1, 1, smp ? nullptr : first + (sg.seq - seq),
+                           smp ? c->samp_row : nullptr));
     HIPCHK(project(c, st, n, nullptr));
-    HIPCHK(ctx_append(c, st, 1, n, c->tmp_pos, nullptr, pt));
-    if (last && !smp) HIPCHK(hipMemcpyAsync(first, c->tmp_argmax, 4, hipMemcpyDeviceToDevice, st));
+    HIPCHK(ctx_append(c, st, 1, n, nullptr, nullptr, nullptr, &segs));
   }
   if (smp) {
-    HIPCHK(launch_set_int(c->tmp_pos + 1, len - 1, st));
+    HIPCHK(launch_set_int(c->tmp_pos + d.max_batch, len[0] - 1, st));
     HIPCHK(launch_sample_first(c->samp_row, sa, first, c->samp, st));
   }
-  HIPCHK(launch_fill_u32((uint32_t*)(c->carry_rec + (size_t)seq * CARRY_REC), 0u, CARRY_REC, st));
+  HIPCHK(launch_fill_u32((uint32_t*)(c->carry_rec + (size_t)seq * CARRY_REC), 0u, (size_t)nseq * CARRY_REC, st));
   return DFLOW_OK;
 }
 }  // namespace
@@ -766,7 +812,7 @@ int prefill_impl(dflow_ctx* c, hipStream_t st, int seq, const int32_t* tok, int 
 // ------------------------------------------------------------------ entry points
 extern "C" int dflow_prefill(dflow_ctx* c, hipStream_t st, int seq, const int32_t* tok, int len,
                              int32_t* first_anchor) {
-  return prefill_impl(c, st, seq, tok, len, nullptr, first_anchor);
+  return prefill_impl(c, st, seq, 1, tok, &len, nullptr, first_anchor);
 }
 
 extern "C" int dflow_prefill_batch(dflow_ctx* c, hipStream_t st, int nseq, const int32_t* tok, const int32_t* len,
@@ -774,21 +820,13 @@ extern "C" int dflow_prefill_batch(dflow_ctx* c, hipStream_t st, int nseq, const
   int rc = check_nseq(c, nseq);
   if (rc) return rc;
   if (!tok || !len || !first_anchor) return fail(DFLOW_EINVAL, "prefill_batch: null argument");
-  for (int s = 0; s < nseq; ++s)   // every length is checked before anything is launched
-    if (len[s] < 1 || (long long)len[s] + c->dm.block > (long long)c->dm.max_pages * PAGE)
-      return fail(len[s] < 1 ? DFLOW_ESHAPE : DFLOW_ECAPACITY, "prefill_batch: sequence %d has %d tokens", s, len[s]);
-  size_t off = 0;
-  for (int s = 0; s < nseq; ++s) {
-    if ((rc = prefill_impl(c, st, s, tok + off, len[s], nullptr, first_anchor + s))) return rc;
-    off += (size_t)len[s];
-  }
-  return DFLOW_OK;
+  return prefill_impl(c, st, 0, nseq, tok, len, nullptr, first_anchor);
 }
 
 extern "C" int dflow_prefill_sampled(dflow_ctx* c, hipStream_t st, int seq, const int32_t* tok, int len,
                                      const dflow_sampler* smp, int32_t* first_token) {
   if (!smp) return fail(DFLOW_EINVAL, "prefill_sampled: null sampler");
-  return prefill_impl(c, st, seq, tok, len, smp, first_token);
+  return prefill_impl(c, st, seq, 1, tok, &len, smp, first_token);
 }
 
 extern "C" int dflow_draft_block(dflow_ctx* c, hipStream_t st, int nseq, const int32_t* anchor_tok,
@@ -841,7 +879,8 @@ extern "C" int dflow_verify_block(dflow_ctx* c, hipStream_t st, int nseq, const 
   const int B = d.block, M = nseq * B;
   HIPCHK(launch_embed(c->bf, block_tok, M, c->w.embed, d.vocab, d.d, c->x, c->status, c->ssq, SSQ_LD, c->rs,
                       d.rms_eps, fout(c, c->xf, d.d), st));
-  HIPCHK(target_forward(c, st, nseq, B, start_pos, c->c.page_table, tgt_argmax, logits, hcap != nullptr));
+  HIPCHK(target_layers(c, st, nseq, B, start_pos, c->c.page_table, hcap != nullptr, nullptr));
+  HIPCHK(target_head(c, st, 0, M, tgt_argmax, logits));
   if (hcap)
     HIPCHK(hipMemcpyAsync(hcap, c->hcap, (size_t)M * d.n_capture * d.d * c->elt, hipMemcpyDeviceToDevice, st));
   return DFLOW_OK;

@@ -692,7 +692,7 @@ __global__ void __launch_bounds__(RB * DH / 4) attn_combine_kernel(AttnParams p)
   float v[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) v[i] = lsum > 0.f ? acc[i] / lsum : 0.f;
-  frag_st4<T>(p.outf, row, hq * DH + d, v);
+  frag_st4<T>(p.outf, p.out_row0 + row, hq * DH + d, v);
 }
 
 // Two rows a workgroup while eight would leave most of the chip idle.

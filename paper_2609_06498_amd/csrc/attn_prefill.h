@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_prefill_kernel(AttnParams p, 
         float y[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) y[e] = ls > 0.f ? (0.f + o[i][d][e]) / ls : 0.f;
-        frag_st4<T>(p.outf, j, c0 + d * 16 + 4 * (lane >> 4), y);
+        frag_st4<T>(p.outf, p.out_row0 + j, c0 + d * 16 + 4 * (lane >> 4), y);
       }
     } else {
       const size_t idx = (((size_t)kvh * p.rg + (r >> 4)) * p.nsplit + split) * 16 + (r & 15);

@@ -43,6 +43,7 @@ struct AttnParams {
   float* part_ml;            // [nseq][Hkv][rg][nsplit][16][2]
   int row_splits;            // 1: the combine merges the splits up to each row's own position (prefill)
   FragOut outf;              // [nseq*Bq, Hq*Dh] output in matrix-core order, the O projection's operand
+  int out_row0;              // output row of row 0
   // pf_wgs extra workgroups (after the nseq*Hkv*nsplit attention ones) read
   // bytes [0, pf_bytes) of pf, pf_per bytes each (multiples of 16), with
   // plain loads that leave them in the memory-side cache for a following

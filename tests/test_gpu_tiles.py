@@ -56,3 +56,33 @@ def test_chunk_rows_bitwise(name):
             continue
         for i, (a, b) in enumerate(zip(ref, got)):
             assert torch.equal(a, b), f"{name}: output {i} with {rows}-row chunks differs from 48-row chunks"
+
+
+@pytest.mark.parametrize("rows", [32, 64, 200, 1024])
+def test_prompts_sharing_chunks_bitwise(rows):
+    """Prompts of a batch share chunks: the caches and first tokens are those of
+    the same prompts taken one at a time (one-row prompts, prompts that end at
+    a chunk's edge and prompts cut by it)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_06498_amd import Runtime
+    dims = DIMS["bf16"]
+    r = np.random.default_rng(9)
+    lens = [1, 63, 130, 6, 1, 300, 11]
+    prompts = [r.integers(0, dims.vocab, size=n).astype(np.int32) for n in lens]
+    w = make_weights(dims, 11)
+    got = []
+    for batch in (False, True):
+        rt = Runtime(dims, 16, len(lens), 400, w, max_rows=rows)
+        first = torch.zeros(len(lens), dtype=torch.int32, device="cuda")
+        if batch:
+            rt.prefill_batch(torch.from_numpy(np.concatenate(prompts)).cuda(), lens, first)
+        else:
+            for s, p in enumerate(prompts):
+                rt.prefill(s, torch.from_numpy(p).cuda(), first[s:s + 1])
+        assert rt.status() == 0
+        got.append([x.clone() for x in (rt.k_pool, rt.v_pool, rt.ck_pool, rt.cv_pool, first)])
+        rt.close()
+    assert bool((got[0][0] != 0).any())
+    for i, (a, b) in enumerate(zip(*got)):
+        assert torch.equal(a, b), f"output {i} differs"
