@@ -52,8 +52,11 @@ __device__ inline Words philox(uint64_t k0, uint64_t k1, uint64_t c0, uint64_t c
       k0 += PH_W0;
       k1 += PH_W1;
     }
-    const uint64_t hi0 = __umul64hi(PH_M0, c0), lo0 = PH_M0 * c0;
-    const uint64_t hi1 = __umul64hi(PH_M1, c2), lo1 = PH_M1 * c2;
+    // one 128-bit product each: both halves from four 32 x 32 multiplies (asked
+    // for apart, the low half cost two more; these run at a quarter of the vector rate and
+    // bound the draws over the vocabulary)
+    const unsigned __int128 p0 = (unsigned __int128)PH_M0 * c0, p1 = (unsigned __int128)PH_M1 * c2;
+    const uint64_t hi0 = (uint64_t)(p0 >> 64), lo0 = (uint64_t)p0, hi1 = (uint64_t)(p1 >> 64), lo1 = (uint64_t)p1;
     const uint64_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
     c0 = n0;
     c1 = lo1;
