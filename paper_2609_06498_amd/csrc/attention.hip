@@ -653,16 +653,13 @@ __global__ void __launch_bounds__(NW * 64) attn_kernel(AttnParams p) {
 
 // out[row, head, :] = sum_split 2^(m_s - M) O_s / sum_split 2^(m_s - M) l_s (m in log2 units)
 // (split order fixed; the split loads are independent and unrolled)
-// Workgroup: RB rows of one head, DH / 4 lanes per row with four channels each.
-// Eight rows write whole 128-byte lines of the matrix-core-order output; one
-// channel per lane and a workgroup per (row, head) took 30 us for 1024 rows of the
-// Qwen3-8B shape (two splits), 17 us for its 512-row round.
-template <typename T, int DH, int RB>
-__global__ void __launch_bounds__(RB * DH / 4) attn_combine_kernel(AttnParams p) {
-  const int row = blockIdx.x * RB + threadIdx.x / (DH / 4);   // s*Bq + j
+// Workgroup: RB rows of one head, DH / CL lanes per row with CL channels each.
+template <typename T, int DH, int RB, int CL>
+__global__ void __launch_bounds__(RB * DH / CL) attn_combine_kernel(AttnParams p) {
+  const int row = blockIdx.x * RB + threadIdx.x / (DH / CL);   // s*Bq + j
   if (row >= p.nseq * p.Bq) return;
   const int hq = blockIdx.y;
-  const int d = threadIdx.x % (DH / 4) * 4;
+  const int d = threadIdx.x % (DH / CL) * CL;
   const int s = row / p.Bq, j = row - s * p.Bq;
   const int G = p.Hq / p.Hkv;
   const int kvh = hq / G, g = hq - kvh * G;
@@ -677,32 +674,39 @@ __global__ void __launch_bounds__(RB * DH / 4) attn_combine_kernel(AttnParams p)
   float M = -INFINITY;
 #pragma unroll 8
   for (int sp = 0; sp < ns; ++sp) M = fmaxf(M, ml[(size_t)sp * 32]);
-  float acc[4] = {0.f, 0.f, 0.f, 0.f}, lsum = 0.f;
+  float acc[CL], lsum = 0.f;
+#pragma unroll
+  for (int i = 0; i < CL; ++i) acc[i] = 0.f;
 #pragma unroll 8
   for (int sp = 0; sp < ns; ++sp) {
     const float m = ml[(size_t)sp * 32];
     const float f = (m == -INFINITY) ? 0.f : exp2f(m - M);   // partial maxima are in log2 units
-    const float4 o = *reinterpret_cast<const float4*>(po + (size_t)sp * 16 * DH);
-    acc[0] += f * o.x;
-    acc[1] += f * o.y;
-    acc[2] += f * o.z;
-    acc[3] += f * o.w;
+    float o[CL];
+    if constexpr (CL == 4) Run4<float>::load(po + (size_t)sp * 16 * DH, o);
+    else o[0] = po[(size_t)sp * 16 * DH];
+#pragma unroll
+    for (int i = 0; i < CL; ++i) acc[i] += f * o[i];
     lsum += f * ml[(size_t)sp * 32 + 1];
   }
-  float v[4];
+  float v[CL];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = lsum > 0.f ? acc[i] / lsum : 0.f;
-  frag_st4<T>(p.outf, p.out_row0 + row, hq * DH + d, v);
+  for (int i = 0; i < CL; ++i) v[i] = lsum > 0.f ? acc[i] / lsum : 0.f;
+  if constexpr (CL == 4) frag_st4<T>(p.outf, p.out_row0 + row, hq * DH + d, v);
+  else frag_st<T>(p.outf, p.out_row0 + row, hq * DH + d, v[0]);
 }
 
-// Two rows a workgroup while eight would leave most of the chip idle.
+// Eight rows with four channels a lane write whole 128-byte lines of the
+// matrix-core-order output (8B shape: 1024 rows with two splits 30 -> 11.5 us, its
+// 512-row round 17 -> 6.6 us).  Small rounds are bound by the latency of the
+// split loads and keep a workgroup per row and one channel a lane (8B round of
+// one sequence: 0.8 us a launch faster than two rows with four channels).
 template <typename T, int DH>
 static hipError_t launch_combine(const AttnParams& p, hipStream_t st) {
   const int rows = p.nseq * p.Bq;
   if (rows * p.Hq >= 8 * 512)
-    hipLaunchKernelGGL((attn_combine_kernel<T, DH, 8>), dim3((rows + 7) / 8, p.Hq), dim3(2 * DH), 0, st, p);
+    hipLaunchKernelGGL((attn_combine_kernel<T, DH, 8, 4>), dim3((rows + 7) / 8, p.Hq), dim3(2 * DH), 0, st, p);
   else
-    hipLaunchKernelGGL((attn_combine_kernel<T, DH, 2>), dim3((rows + 1) / 2, p.Hq), dim3(DH / 2), 0, st, p);
+    hipLaunchKernelGGL((attn_combine_kernel<T, DH, 1, 1>), dim3(rows, p.Hq), dim3(DH), 0, st, p);
   return hipGetLastError();
 }
 
