@@ -150,8 +150,10 @@ hipError_t launch_rmsnorm(bool isbf, bool in_f32, const void* x, int ldx, int M,
 // a row's loads and stores are 16 and 8 bytes a lane and its sum of squares
 // takes one lane's eight terms and log2(DH / 8) exchanges.  Consecutive rows
 // together, because their keys and values share the cache lines of a page.
-// Bound by memory traffic; one wave per (row, head) with 4-byte accesses
-// took 20.8 us for 1024 rows of the Qwen3-8B shape, 9.7 us for 512 of the 1.7B shape.
+// Bound by memory traffic, the two-byte value stores most of all (a lane's
+// channels lie 16 bytes apart in fragment order): 16.7 us for 1024 rows of the
+// Qwen3-8B shape, where one wave per (row, head) with 4-byte accesses took 20.8; 64
+// rows of the 32B shape 5.5 us.
 template <typename T, int DH>
 __global__ void __launch_bounds__(256) qk_rope_kernel(RopeParams p) {
   constexpr int LPR = DH / 8, HALF = DH / 2;
