@@ -223,7 +223,9 @@ int dflow_attention_split(const dflow_ctx* ctx, int* chunk_keys, int* chunks);
 /* Prompt processing for sequence slot `seq` (set-up, not part of the round):
  * target KV for positions 0..len-1, fused features and drafter context K/V
  * for the same positions, and first_anchor[0] = the target's greedy token
- * after the prompt.  Clears the slot's carry record.  tok: device [len]. */
+ * after the prompt.  Clears the slot's carry record.  tok: device [len].
+ * It may be issued anywhere between the calls of a round of other slots: the
+ * round's captured states and features are kept apart from the prompt's. */
 int dflow_prefill(dflow_ctx* ctx, hipStream_t stream, int seq, const int32_t* tok, int len, int32_t* first_anchor);
 
 /* Prompt processing of nseq sequences in slots 0..nseq-1: the results of

@@ -82,13 +82,16 @@ struct dflow_ctx {
   float* rs;             // [mmax] RMSNorm row scales of x (launches of more than SPLIT_MIN_ROWS rows)
   unsigned* arrive;      // arrival counters of the residual GEMMs; every launch leaves them at 0
   float* kpart;          // K-part partial sums of the split residual and gate/up GEMMs
-  // Matrix-core-order copies of the projections' A operands (mmax rows,
-  // rounded up to 16): x (QKV, gate/up, LM heads), attention output (O), SwiGLU
-  // / relay hidden (down, relay W2), captured states (W_c), relay input (W1),
-  // projected features (drafter context K/V).  A copy is read only by the call
-  // that wrote it, or -- captured states, features -- by the next call of the
-  // round (accept after verify, commit after accept).
-  void *xf, *attnf, *actf, *hcapf, *uf, *ff;
+  // Matrix-core-order copies of the projections' A operands (rows rounded up to
+  // 16): x (QKV, gate/up, LM heads), attention output (O), SwiGLU / relay hidden
+  // (down, relay W2), relay input (W1), captured states (W_c), projected
+  // features (drafter context K/V).  A copy is read only by the call that wrote
+  // it, except the round's captured states (written by verify, read by accept)
+  // and features (written by accept, read by commit).  A prompt may be processed
+  // between those calls, so prefill has captured states and features of its own.
+  void *xf, *attnf, *actf, *uf;   // mmax rows (uf: the round's)
+  void *hcapf, *ff;               // the round's rows
+  void *pre_hcapf, *pre_ff;       // a prefill chunk's rows
 
   // kernel timing record (dflow_profile)
   bool prof = false;
@@ -228,15 +231,21 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* lm_groups_out) {
   }
   {   // 27..32 matrix-core-order operand copies
     const size_t fr = (size_t)((mmax + 15) / 16 * 16) * elt;
+    const size_t round_fr = (size_t)((rows_round + 15) / 16 * 16) * elt;
     add(fr * d->d);                                       // 27 x
     add(fr * qd);                                         // 28 attention output
     add(fr * (d->ffn > d->relay_hidden ? d->ffn : d->relay_hidden));   // 29 SwiGLU / relay hidden
-    add(fr * d->n_capture * d->d);                        // 30 captured states
-    add(fr * 3 * d->d);                                   // 31 relay input
-    add(fr * d->d);                                       // 32 projected features
+    add(round_fr * d->n_capture * d->d);                  // 30 captured states of the round
+    add(round_fr * 3 * d->d);                             // 31 relay input
+    add(round_fr * d->d);                                 // 32 projected features of the round
   }
   add((size_t)mmax * 4);                                  // 33 rs: RMSNorm row scales
   add(MAX_ROWS / 64 * 4);                                 // 34 arrival counters of the residual GEMMs (zero between launches)
+  {   // 35, 36 captured states and features of a prefill chunk
+    const size_t pre_fr = (size_t)((d->max_rows + 15) / 16 * 16) * elt;
+    add(pre_fr * d->n_capture * d->d);
+    add(pre_fr * d->d);
+  }
   L.total = o;
   if (nsplit_out) *nsplit_out = nsplit;
   if (lm_groups_out) *lm_groups_out = lm_groups;
@@ -343,6 +352,8 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   c->ff = b + L.off[32];
   c->rs = (float*)(b + L.off[33]);
   c->arrive = (unsigned*)(b + L.off[34]);
+  c->pre_hcapf = b + L.off[35];
+  c->pre_ff = b + L.off[36];
 
   // RoPE table: angle p * theta^(-2i/Dh) evaluated in double
   const int half = dims->head_dim / 2;
@@ -635,8 +646,8 @@ hipError_t decoder_layer(dflow_ctx* c, hipStream_t st, const dflow_layer& L, int
 }
 
 // Target layers over rows already embedded in x (segs: a prefill chunk's
-// segments).  The captured states go to the matrix-core-order operand
-// of W_c, and with `rows_out` to the row-major c->hcap too.
+// segments).  The captured states go to the matrix-core-order operand of W_c
+// (the round's or prefill's), and with `rows_out` to the row-major c->hcap too.
 hipError_t target_layers(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const int* start_pos,
                          const int* page_table, bool rows_out, const std::vector<Seg>* segs) {
   const dflow_dims& d = c->dm;
@@ -646,7 +657,7 @@ hipError_t target_layers(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const i
     void* cap = nullptr;
     FragOut capf{nullptr, 0, 0};
     if (ci < d.n_capture && d.capture_layers[ci] == l) {
-      capf = fout(c, c->hcapf, d.n_capture * d.d, ci * d.d);
+      capf = fout(c, segs ? c->pre_hcapf : c->hcapf, d.n_capture * d.d, ci * d.d);
       if (rows_out) cap = (char*)c->hcap + (size_t)ci * d.d * c->elt;
       ++ci;
     }
@@ -674,21 +685,23 @@ hipError_t target_head(dflow_ctx* c, hipStream_t st, int lm_row0, int lm_rows, i
   return launch_argmax_reduce(c->amax, c->lm_groups, lm_rows, c->amax_part, c->counters, argmax_out, nullptr, st);
 }
 
-// F = RMSNorm(W_c [captured states]) for M rows -> c->ff and, row-major, out (null: no copy)
+// F = RMSNorm(W_c [captured states]) for M rows: the round's, to c->ff and
+// row-major to out, or with out null a prefill chunk's, to c->pre_ff only
 hipError_t project(dflow_ctx* c, hipStream_t st, int M, void* out) {
   const dflow_dims& d = c->dm;
   hipError_t e;
   const int K = d.n_capture * d.d;
   Frag fr;
-  fr.a = c->hcapf;
+  fr.a = out ? c->hcapf : c->pre_hcapf;
   if ((e = gemm(c, st, EPI_STORE_F32, nullptr, K, c->w.w_c, M, d.d, K, c->fproj, d.d, nullptr, 0, nullptr, 0,
                 nullptr, nullptr, 0, NormIn(), nullptr, 1, fr)))
     return e;
-  return launch_rmsnorm(c->bf, true, c->fproj, d.d, M, d.d, c->w.g_c, d.rms_eps, out, d.d, fout(c, c->ff, d.d),
-                        st);
+  return launch_rmsnorm(c->bf, true, c->fproj, d.d, M, d.d, c->w.g_c, d.rms_eps, out, d.d,
+                        fout(c, out ? c->ff : c->pre_ff, d.d), st);
 }
 
-// Drafter context K/V of the feature rows in c->ff (nseq x Bq) at start_pos + j for rows j <= row_limit[s].
+// Drafter context K/V of the feature rows (nseq x Bq, the round's or with segs
+// a prefill chunk's) at start_pos + j for rows j <= row_limit[s].
 // All drafter layers at once: one GEMM over the stacked [Wk; Wv] of every
 // layer, then K-norm + RoPE + paged write for every layer in one launch.
 hipError_t ctx_append(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const int* start_pos,
@@ -699,7 +712,7 @@ hipError_t ctx_append(dflow_ctx* c, hipStream_t st, int nseq, int Bq, const int*
   const int ncols = d.n_draft_layers * 2 * c->kv_dim;
   hipError_t e;
   Frag fr;
-  fr.a = c->ff;
+  fr.a = segs ? c->pre_ff : c->ff;
   if ((e = gemm(c, st, EPI_STORE_T, nullptr, d.d, c->w.draft_wkv_ctx, M, ncols, d.d, c->ctxkv, ncols, nullptr, 0,
                 nullptr, 0, nullptr, nullptr, 0, NormIn(), nullptr, 1, fr)))
     return e;
