@@ -771,7 +771,7 @@ int sampler_args(const dflow_ctx* c, const dflow_sampler* smp, const int32_t* po
 int prefill_impl(dflow_ctx* c, hipStream_t st, int seq, int nseq, const int32_t* tok, const int32_t* len,
                  const dflow_sampler* smp, int32_t* first) {
   if (!c || !tok || !first) return fail(DFLOW_EINVAL, "prefill: null argument");
-  if (seq < 0 || seq + nseq > c->dm.max_batch) return fail(DFLOW_EINVAL, "prefill: seq %d", seq);
+  if (seq < 0 || seq > c->dm.max_batch - nseq) return fail(DFLOW_EINVAL, "prefill: seq %d", seq);
   for (int i = 0; i < nseq; ++i) {   // every length is checked before anything is launched
     if (len[i] < 1) return fail(DFLOW_ESHAPE, "prefill: sequence %d has %d tokens", seq + i, len[i]);
     if ((long long)len[i] + c->dm.block > (long long)c->dm.max_pages * PAGE)

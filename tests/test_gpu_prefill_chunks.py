@@ -54,3 +54,23 @@ def test_prefill_chunk_size_invariance():
             continue
         for i, (a, b) in enumerate(zip(ref, out)):
             assert np.array_equal(a, b), f"max_rows {mr}: output {i} differs from the 128-row chunks"
+
+
+@pytest.mark.parametrize("seq", [-2**31, -1, 2, 2**31 - 1])
+def test_prefill_refuses_slots_outside_the_batch(seq):
+    """Nothing is launched for a slot that the context does not have, the largest int among them."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_06498_amd import DFlowError, Runtime
+    wl = get_config("tiny-f32")
+    rt = Runtime(wl.dims, wl.block, 2, 64, make_weights(wl.dims, wl.seed_w))
+    tok = torch.zeros(4, dtype=torch.int32, device="cuda")
+    first = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    smp = rt.sampler(1.0, 5, torch.zeros(1, dtype=torch.int64, device="cuda"))
+    with pytest.raises(DFlowError, match="seq"):
+        rt.prefill(seq, tok, first)
+    with pytest.raises(DFlowError, match="seq"):
+        rt.prefill_sampled(seq, tok, smp, first)
+    assert int(first) == -7 and rt.status() == 0
+    assert not bool((rt.k_pool != 0).any())
+    rt.close()
