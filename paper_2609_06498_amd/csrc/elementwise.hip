@@ -209,11 +209,17 @@ __global__ void __launch_bounds__(256) qk_rope_kernel(RopeParams p) {
     return;
   }
   const T* gain = reinterpret_cast<const T*>(is_q ? p.q_norm : (p.k_norms ? p.k_norms[layer] : p.k_norm));
-  float ss = 0.f;
+  // Sum of squares as a binary tree over the rotation pairs (distances HALF / 2
+  // .. 1; a lane's own four pairs are the last two levels): permuting a row's
+  // pairs by any xor leaves it unchanged.
+  float sq[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) ss += x[0][i] * x[0][i] + x[1][i] * x[1][i];
+  for (int i = 0; i < 4; ++i) {
+    sq[i] = fmaf(x[1][i], x[1][i], x[0][i] * x[0][i]);
 #pragma unroll
-  for (int o = LPR / 2; o >= 1; o >>= 1) ss += __shfl_xor(ss, o, 64);
+    for (int o = LPR / 2; o >= 1; o >>= 1) sq[i] += __shfl_xor(sq[i], o, 64);
+  }
+  const float ss = (sq[0] + sq[2]) + (sq[1] + sq[3]);
   const float r = rsqrtf(ss / (float)DH + p.eps);
   const float* cs = reinterpret_cast<const float*>(p.rope + (size_t)pos * HALF + c);
   float ang[8];
@@ -224,8 +230,11 @@ __global__ void __launch_bounds__(256) qk_rope_kernel(RopeParams p) {
   for (int i = 0; i < 4; ++i) {
     const float y1 = x[0][i] * r * TT<T>::ld(gain, c + i);
     const float y2 = x[1][i] * r * TT<T>::ld(gain, c + HALF + i);
-    o1[i] = y1 * ang[2 * i] - y2 * ang[2 * i + 1];
-    o2[i] = y2 * ang[2 * i] + y1 * ang[2 * i + 1];
+    // fused operations written out, one form per storage type: the result does
+    // not change with the compiler's choice of contraction
+    o1[i] = fmaf(y1, ang[2 * i], -(y2 * ang[2 * i + 1]));
+    if constexpr (sizeof(T) == 2) o2[i] = fmaf(y1, ang[2 * i + 1], y2 * ang[2 * i]);
+    else o2[i] = fmaf(y2, ang[2 * i], y1 * ang[2 * i + 1]);
   }
   if (is_q) {
     T* q = reinterpret_cast<T*>(p.q_out) + (size_t)row * p.nq * DH + (size_t)h * DH + c;
