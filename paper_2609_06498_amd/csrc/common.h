@@ -228,7 +228,7 @@ template <int OFF>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const void* base, uint32_t voff) {
   asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base),
                "n"(OFF)
-               : "memory", "scc");
+               : "memory", "scc", "m0");
 }
 // wait until at most N vector-memory operations of this wave are in flight and
 // its LDS reads are done, then meet the workgroup's other waves
