@@ -8,7 +8,9 @@ written directly, or merged from one or two partials, depending on the chunk.
   The chunk sizes sit at the edges of the tiles
 (64 and 128 rows), of the split rules (49, 256/257, 512/513 rows) and off the
 16-row tiles; the widths give odd strip and k-tile counts, K ranges of unequal
-length and reductions shorter than the load ring."""
+length and reductions shorter than the load ring.  A prompt's LM head has one row
+and never reaches a tile, and no prompt runs the relay: rounds of many sequences
+do, compared with the same sequences a few at a time."""
 import numpy as np
 import pytest
 
@@ -22,7 +24,7 @@ pytestmark = pytest.mark.gpu
 DIMS = {
     "bf16": get_config("small-bf16").dims,
     "f32": get_config("small-f32").dims,
-    # 3, 4 and 5 k tiles per projection, 17 strips of vocabulary
+    # 3, 4 and 5 k tiles per projection
     "bf16-narrow": ModelDims("bf16", 96, 2, 2, 1, 64, 160, 272, 1, (0, 1)),
     "f32-narrow": ModelDims("f32", 48, 2, 2, 1, 64, 112, 272, 1, (0, 1)),
     # gate/up of 257 column tiles: 256-row tiles at 1000 and 1024 rows
@@ -86,3 +88,46 @@ def test_prompts_sharing_chunks_bitwise(rows):
     assert bool((got[0][0] != 0).any())
     for i, (a, b) in enumerate(zip(*got)):
         assert torch.equal(a, b), f"output {i} differs"
+
+
+@pytest.mark.parametrize("b", [25, 50])
+def test_round_rows_bitwise(b):
+    """Rounds of 250 and 500 rows (the last 16-row and 256-row tiles not full)
+    against the same sequences four at a time (40 rows, the weight-streaming
+    kernels).  The LM heads take the 256 x 128 tile (3073 strips: 385 strip
+    tiles, the last of a single strip).  The second round runs the relay, whose two projections take the
+    tiles' bias epilogues."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_06498_amd import Runtime
+    from paper_2609_06498_amd.session import Session
+    dims = ModelDims("bf16", 96, 2, 2, 1, 64, 160, 49168, 1, (0, 1))
+    B, rounds = 10, 2
+    r = np.random.default_rng(13)
+    prompts = [r.integers(0, dims.vocab, size=n).astype(np.int32) for n in r.integers(3, 40, size=b)]
+    rt = Runtime(dims, B, b, 64 + rounds * B, make_weights(dims, 11))
+
+    def run(seqs):
+        s = Session(rt, len(seqs))
+        s.prefill([prompts[i] for i in seqs])
+        out = []
+        for _ in range(rounds):
+            lg = torch.zeros(len(seqs) * B, dims.vocab, dtype=torch.float32, device="cuda")
+            dl = torch.zeros_like(lg)
+            s.round(True, draft_logits=dl, logits=lg)
+            out.append([dl.view(len(seqs), B, -1), lg.view(len(seqs), B, -1)] +
+                       [x.clone() for x in (s.block, s.tgt, s.committed, s.accept, s.n_carry, s.seq_len)])
+        assert rt.status() == 0
+        return out
+
+    print(f"[tiles] round of {b * B} rows", flush=True)
+    many = run(list(range(b)))
+    assert int(many[0][6].max()) > 0        # something is carried, so the second round relays rows
+    for lo in range(0, b, 4):
+        seqs = list(range(lo, min(lo + 4, b)))
+        for k, (x, y) in enumerate(zip(run(seqs), many)):
+            for i, (p, q) in enumerate(zip(x, y)):
+                assert torch.equal(p, q[lo:lo + len(seqs)]), f"sequences {seqs}, round {k}: output {i} differs"
+    # the argmax of the logits themselves
+    assert torch.equal(many[1][1].argmax(-1).int(), many[1][3])
+    rt.close()
