@@ -368,11 +368,11 @@ __global__ void __launch_bounds__(512) gemm_kernel(GemmParams p) {
 // smaller ones are for row counts and widths that would leave units idle (8B
 // QKV at 128 rows 18.6 us at 128 x 128, 15.5 at 128 x 64; down at 1024 rows 107 us
 // at 128 x 128, 142 at 256 x 128).
-typedef TileShape<2, 4, 4, 2, 1, 2> Tile128x128;
-typedef TileShape<2, 2, 4, 2, 1, 3> Tile128x64;
-typedef TileShape<1, 4, 4, 2, 1, 3> Tile64x128;
-typedef TileShape<2, 2, 2, 2, 1, 4> Tile64x64;
-typedef TileShape<4, 2, 4, 4, 1, 1> Tile256x128;
+typedef TileShape<2, 4, 4, 2, 2> Tile128x128;
+typedef TileShape<2, 2, 4, 2, 3> Tile128x64;
+typedef TileShape<1, 4, 4, 2, 3> Tile64x128;
+typedef TileShape<2, 2, 2, 2, 4> Tile64x64;
+typedef TileShape<4, 2, 4, 4, 1> Tile256x128;
 struct TileCost { int bm, bs; double t1, tn; };
 constexpr TileCost TILES[] = {{128, 8, 0.26, 0.28}, {128, 4, 0.18, 0.165}, {64, 8, 0.19, 0.165}, {64, 4, 0.15, 0.115},
                               {256, 8, 0.38, 0.48}};

@@ -1,19 +1,18 @@
 // Tiled GEMM for many rows (included by gemm.hip): Y[M, N] = A[M, K] W[N, K]^T
 // with A in its matrix-core-order copy (afrag_off) and W packed.
 //
-// Workgroup tile: 32 WM rows x 2 WN strips of 16 columns, four waves in a 2 x 2
-// grid of 16 WM rows x WN strips each.  A stage is two k tiles of both
-// operands, 2 * (2 WM + 2 WN) tiles of 1 KB, already in fragment order in
-// memory, so each goes to LDS with one load-to-LDS instruction per wave (no
-// registers, no LDS writes by the waves); NS stages sit in an LDS ring, NS - 1
-// of them in flight.
+// Workgroup tile: NWM x NWN waves of 16 WM rows x WN strips of 16 columns each
+// (1 x 4 to 4 x 2 waves, 64 x 64 to 256 x 128).  A stage is one k tile of both
+// operands, a 1 KB tile per 16 rows and per strip, already in fragment order in
+// memory, so each goes to LDS with one load-to-LDS instruction of a wave (no
+// registers, no LDS writes by the waves).  NS stages sit in an LDS ring.
 //
-// One barrier per stage, in its middle: a wave first reads its fragments of
-// the stage's second k tile while the matrix cores work on the first, then
-// waits for the next stage's loads and meets the others; after the barrier
-// every wave has the stage in registers, so its ring slot takes the loads of
-// stage s + NS, the first fragments of stage s + 1 are read, and the matrix
-// cores work on the second k tile meanwhile.
+// A step works on stage s, whose fragments are in registers or on their way
+// there.  It waits until this wave's loads of stage s + 1 have landed (those of s
+// + 2 .. s + NS - 1 stay in flight) and its own LDS reads are done, and meets the
+// other waves: every wave has now read stage s and sees s + 1 whole.  The ring
+// slot of s takes the loads of stage s + NS, the fragments of s + 1 are read, and
+// the matrix cores multiply stage s meanwhile.  One barrier per stage.
 //
 // Arithmetic: the K loop runs the weight-streaming kernel's wave ranges
 // (gemm_shape) in order, each range one matrix-core chain from zero, folded
@@ -38,17 +37,16 @@ template <> __device__ __forceinline__ void pair_st<float>(float* p, float a, fl
 
 constexpr size_t TILE_LDS_CU = 156 * 1024;
 
-// Tile shape: NWM x NWN waves of 16 WM rows x WN strips, KPS k tiles per stage,
-// OCC workgroups per compute unit.
-template <int NWM_, int NWN_, int WM_, int WN_, int KPS_, int OCC_>
+// Tile shape: NWM x NWN waves of 16 WM rows x WN strips, OCC workgroups per compute unit.
+template <int NWM_, int NWN_, int WM_, int WN_, int OCC_>
 struct TileShape {
-  static constexpr int NWM = NWM_, NWN = NWN_, WM = WM_, WN = WN_, KPS = KPS_, OCC = OCC_;
+  static constexpr int NWM = NWM_, NWN = NWN_, WM = WM_, WN = WN_, OCC = OCC_;
   static constexpr int NW = NWM * NWN, BM = 16 * NWM * WM, BS = NWN * WN;   // waves, rows, strips
-  static constexpr int AT = NWM * WM, TPK = AT + BS;                        // 1 KB tiles per k tile: A, both
-  static constexpr int LPW = TPK * KPS / NW;                                // loads per wave and stage
-  static constexpr size_t STAGE = (size_t)TPK * KPS * 1024;
+  static constexpr int AT = NWM * WM, TPS = AT + BS;                        // 1 KB tiles per stage: A, both
+  static constexpr int LPW = TPS / NW;                                      // loads per wave and stage
+  static constexpr size_t STAGE = (size_t)TPS * 1024;
   static constexpr int FIT = (int)(TILE_LDS_CU / OCC / STAGE), NS = FIT < 8 ? FIT : 8;   // ring depth
-  static_assert(TPK * KPS % NW == 0 && NS >= 3 && (NS - 1) * LPW < 64, "loads, ring depth, vmcnt range");
+  static_assert(TPS % NW == 0 && NS >= 3 && (NS - 1) * LPW < 64, "loads, ring depth, vmcnt range");
 };
 
 // Residual epilogue: rnd(sum + R) to Y (and Y2) and the matrix-core-order
@@ -149,7 +147,7 @@ __device__ __forceinline__ void resid_epilogue(const GemmParams& p, const f32x4_
 template <typename T, int EPI, typename S>
 __global__ void __launch_bounds__(S::NW * 64, S::OCC * S::NW / 4) gemm_tile_kernel(GemmParams p, int nw, int mt,
                                                                                    int units) {
-  constexpr int WM = S::WM, WN = S::WN, NS = S::NS, LPW = S::LPW, KPS = S::KPS;
+  constexpr int WM = S::WM, WN = S::WN, NS = S::NS, LPW = S::LPW;
   constexpr uint32_t STAGE = (uint32_t)S::STAGE;
   extern __shared__ __align__(16) unsigned char tile_smem[];
   const int lane = threadIdx.x & 63;
@@ -167,15 +165,15 @@ __global__ void __launch_bounds__(S::NW * 64, S::OCC * S::NW / 4) gemm_tile_kern
   const int kpart = (p.ktiles + ks - 1) / ks;
   const int k0 = min(p.ktiles, h * kpart), k1 = min(p.ktiles, k0 + kpart);
   const int kper = max(1, (k1 - k0 + nw - 1) / nw);
-  const int nst = (k1 - k0 + KPS - 1) / KPS;
+  const int nst = k1 - k0;                     // stages
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)tile_smem + w * 1024;
 
-  // this wave's loads of a stage: tiles w + NW i of its [k tile][row tiles, strips]
+  // this wave's loads of a stage: tiles w + NW i of its row tiles, then strips
   // (clamped to valid ones: rows and strips past the end are never stored)
   const char* src[LPW];
 #pragma unroll
   for (int i = 0; i < LPW; ++i) {
-    const int idx = (w + S::NW * i) % S::TPK;
+    const int idx = w + S::NW * i;
     src[i] = idx < S::AT ? (const char*)p.Af + (size_t)min(rt0 + idx, (p.M + 15) / 16 - 1) * p.ktiles * 1024
                          : (const char*)p.W + (size_t)min(nt0 + idx - S::AT, p.ntiles - 1) * p.ktiles * 1024;
   }
@@ -183,9 +181,7 @@ __global__ void __launch_bounds__(S::NW * 64, S::OCC * S::NW / 4) gemm_tile_kern
   const uint32_t voff = lane * 16;
   auto issue = [&]<int SLOT>(std::integral_constant<int, SLOT>, int s, uint32_t base) {
     static_for<LPW>([&]<int I>(std::integral_constant<int, I>) {
-      // (an odd tail of a two-tile stage reads its last k tile twice)
-      const int kt = KPS == 1 ? k0 + s : min(k0 + KPS * s + (w + S::NW * I) / S::TPK, k1 - 1);
-      load_to_lds<SLOT * (int)STAGE + S::NW * I * 1024>(base, src[I], (uint32_t)kt * 1024 + voff);
+      load_to_lds<SLOT * (int)STAGE + S::NW * I * 1024>(base, src[I], (uint32_t)(k0 + s) * 1024 + voff);
     });
   };
 
@@ -206,9 +202,9 @@ __global__ void __launch_bounds__(S::NW * 64, S::OCC * S::NW / 4) gemm_tile_kern
       }
     left = kper;
   };
-  u32x4_t fa[2][WM], fb[2][WN];                 // fragments of the k tile being multiplied and of the next one
-  auto frags = [&](int slot, int kk, int f) {
-    const u32x4_t* t = reinterpret_cast<const u32x4_t*>(tile_smem + (size_t)slot * STAGE + kk * S::TPK * 1024);
+  u32x4_t fa[2][WM], fb[2][WN];                 // fragments of the stage being multiplied and of the next one
+  auto frags = [&](int slot, int f) {
+    const u32x4_t* t = reinterpret_cast<const u32x4_t*>(tile_smem + (size_t)slot * STAGE);
 #pragma unroll
     for (int j = 0; j < WN; ++j) fb[f][j] = t[(S::AT + wn * WN + j) * 64 + lane];
 #pragma unroll
@@ -227,56 +223,37 @@ __global__ void __launch_bounds__(S::NW * 64, S::OCC * S::NW / 4) gemm_tile_kern
     for (int s = 0; s < pre; ++s) issue(Z, s, lds0 + s * STAGE);
     if (nst >= NS) wait_barrier<(NS - 1) * LPW>();
     else wait_barrier<0>();
-    frags(0, 0, 0);
-    // Steady state, unrolled over the ring: stage s is in registers (or its
-    // last reads are under way); wait for stage s + 1 (s + 2 .. s + NS - 1 stay
-    // in flight), meet the other waves, refill the slot of s, read stage s + 1.
-    constexpr int U = KPS == 2 || NS % 2 == 0 ? NS : 2 * NS;
+    frags(0, 0);
+    // steady state, unrolled over the ring (and the two fragment sets)
+    constexpr int U = NS % 2 == 0 ? NS : 2 * NS;
     int s = 0;
     for (; s + NS + U - 1 < nst; s += U)
       static_for<U>([&]<int I>(std::integral_constant<int, I>) {
         constexpr int slot = I % NS, nxt = (I + 1) % NS;
-        if constexpr (KPS == 2) {
-          frags(slot, 1, 1);
-          mul(0);
-        }
         wait_barrier<(NS - 2) * LPW>();
         issue(std::integral_constant<int, slot>{}, s + I + NS, lds0);
-        frags(nxt, 0, KPS == 2 ? 0 : (I & 1) ^ 1);
-        mul(KPS == 2 ? 1 : I & 1);
+        frags(nxt, (I & 1) ^ 1);
+        mul(I & 1);
       });
-    // the rest, two k tiles at a time
+    // the rest, two stages at a time
     int slot = 0;                               // s is a multiple of NS here
     auto advance = [&](int x, int f) {
       if (x + NS <= nst) wait_barrier<(NS - 2) * LPW>();
       else wait_barrier<0>();
       if (x + NS < nst) issue(Z, x + NS, lds0 + slot * STAGE);
       slot = slot + 1 == NS ? 0 : slot + 1;
-      frags(slot, 0, f);
+      frags(slot, f);
     };
-    if constexpr (KPS == 2) {
-      for (; s + 1 < nst; ++s) {
-        frags(slot, 1, 1);
-        mul(0);
-        advance(s, 0);
-        mul(1);
-      }
-      const bool two = (k1 - k0) % 2 == 0;      // the last stage has both k tiles
-      if (two) frags(slot, 1, 1);
+    for (; s + 2 < nst; s += 2) {
+      advance(s, 1);
       mul(0);
-      if (two) mul(1);
-    } else {
-      for (; s + 2 < nst; s += 2) {
-        advance(s, 1);
-        mul(0);
-        advance(s + 1, 0);
-        mul(1);
-      }
-      const bool two = s + 1 < nst;
-      if (two) advance(s, 1);
-      mul(0);
-      if (two) mul(1);
+      advance(s + 1, 0);
+      mul(1);
     }
+    const bool two = s + 1 < nst;
+    if (two) advance(s, 1);
+    mul(0);
+    if (two) mul(1);
     if (left != kper) fold();                   // the last, shorter range
   }
   // (ranges past the end are empty: their partial sums are +0, and adding +0
