@@ -52,7 +52,7 @@ struct dflow_ctx {
   int mmax, rows_round;
   int G, nsplit;
   int split_keys;            // keys per attention chunk (split_keys_for)
-  int round_chunks;          // attention chunks per split in the round calls (prefill: 1)
+  int round_chunks;          // attention chunks per split in the round calls
   int lm_groups;
   int qkv_ks;                // K parts of the QKV projection (fp32 partial sums, added by the consumers)
   int cus;                   // compute units of the device (launch balance decisions)
@@ -162,8 +162,14 @@ int validate(const dflow_dims* d) {
   return DFLOW_OK;
 }
 
+// workspace buffers, in order (the context's members of the same names describe them)
+enum Buf {
+  W_X, W_QKV, W_Q, W_HCAP, W_F, W_FPROJ, W_BG, W_PART_O, W_PART_ML, W_ROPE, W_AMAX, W_CARRY, W_TMP_POS, W_SSQ,
+  W_AMAX_PART, W_COUNTERS, W_CTXKV, W_DKNORM, W_SAMP, W_SAMP_ROW, W_KPART, W_XF, W_ATTNF, W_ACTF, W_HCAPF,
+  W_UF, W_FF, W_RS, W_ARRIVE, W_PRE_HCAPF, W_PRE_FF, W_COUNT
+};
 struct Layout {
-  size_t off[40];
+  size_t off[W_COUNT];
   size_t total;
 };
 
@@ -185,35 +191,28 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* lm_groups_out) {
   const int lm_groups = (d->vocab / 16 + 1) / 2;   // gemm_shape: two strips per argmax workgroup
   Layout L;
   size_t o = 0;
-  int i = 0;
-  auto add = [&](size_t bytes) { L.off[i++] = o; o += align256(bytes); };
-  add((size_t)mmax * d->d * elt);                      // 0 x
-  add(0);                                              // 1 unused
-  add((size_t)2 * mmax * qkvn * 4);                    // 2 qkv: up to two fp32 K parts
-  add((size_t)mmax * qd * elt);                        // 3 q
-  add(0);                                              // 4 unused
-  add(0);                                              // 5 unused
-  add((size_t)mmax * d->n_capture * d->d * elt);       // 6 hcap (row-major copy, when the caller asks for it)
-  add((size_t)rows_round * d->d * elt);                // 7 f (projected features of the last verify)
-  add(0);                                              // 8 unused
-  add((size_t)mmax * d->d * 4);                        // 9 fproj
-  add((size_t)rows_round * 2 * d->d * 4);              // 10 bg
-  add(items * d->n_kv_heads * 16 * d->head_dim * 4);    // 11 part_o
-  add(items * d->n_kv_heads * 32 * 4);                  // 12 part_ml
-  add((size_t)d->max_pages * PAGE * (d->head_dim / 2) * sizeof(float2));  // 13 rope
-  add((size_t)lm_groups * mmax * 8);                   // 14 amax: [lm_groups][rows] argmax keys
-  add((size_t)d->max_batch * CARRY_REC * 4);           // 15 carry_rec
-  add(4);                                              // 16 unused (the status word is the caller's)
-  add((size_t)(d->max_batch + 1) * 4);                 // 17 tmp_pos
-  add(0);                                              // 18 unused
-  add((size_t)mmax * SSQ_LD * 4);                      // 19 ssq: per-strip sums of squares of the residual rows
-  add((size_t)ARGMAX_SPLITS * mmax * 8);               // 20 amax_part: [split][row] partial argmax keys
-  add(ARGMAX_BLOCKS * 4);                              // 21 counters (zero between launches)
-  add((size_t)mmax * d->n_draft_layers * 2 * kvd * elt);   // 22 ctxkv: drafter-context K/V rows of all drafter layers
-  add((size_t)(d->n_draft_layers > 0 ? d->n_draft_layers : 1) * sizeof(void*));   // 23 drafter K-norm gain pointers
-  add(samp_workspace_bytes(d->vocab, mmax, d->max_batch));   // 24 sampling partials (log-sum-exp, draw keys)
-  add((size_t)d->vocab * 4);                           // 25 fp32 logits of a prompt's last row (sampled prefill)
-  {   // 26 K-part partial sums of the split GEMMs: residual (O, down), gate/up and the other projections
+  auto add = [&](Buf b, size_t bytes) { L.off[b] = o; o += align256(bytes); };
+  add(W_X, (size_t)mmax * d->d * elt);
+  add(W_QKV, (size_t)2 * mmax * qkvn * 4);   // up to two fp32 K parts
+  add(W_Q, (size_t)mmax * qd * elt);
+  add(W_HCAP, (size_t)rows_round * d->n_capture * d->d * elt);   // row-major copy, when verify's caller asks for it
+  add(W_F, (size_t)rows_round * d->d * elt);   // projected features of the last verify
+  add(W_FPROJ, (size_t)mmax * d->d * 4);
+  add(W_BG, (size_t)rows_round * 2 * d->d * 4);
+  add(W_PART_O, items * d->n_kv_heads * 16 * d->head_dim * 4);
+  add(W_PART_ML, items * d->n_kv_heads * 32 * 4);
+  add(W_ROPE, (size_t)d->max_pages * PAGE * (d->head_dim / 2) * sizeof(float2));
+  add(W_AMAX, (size_t)lm_groups * mmax * 8);   // [lm_groups][rows] argmax keys
+  add(W_CARRY, (size_t)d->max_batch * CARRY_REC * 4);
+  add(W_TMP_POS, (size_t)(d->max_batch + 1) * 4);
+  add(W_SSQ, (size_t)mmax * SSQ_LD * 4);   // per-strip sums of squares of the residual rows
+  add(W_AMAX_PART, (size_t)ARGMAX_SPLITS * mmax * 8);   // [split][row] partial argmax keys
+  add(W_COUNTERS, ARGMAX_BLOCKS * 4);   // zero between launches
+  add(W_CTXKV, (size_t)mmax * d->n_draft_layers * 2 * kvd * elt);   // drafter-context K/V rows of all drafter layers
+  add(W_DKNORM, (size_t)(d->n_draft_layers > 0 ? d->n_draft_layers : 1) * sizeof(void*));
+  add(W_SAMP, samp_workspace_bytes(d->vocab, mmax, d->max_batch));   // sampling partials (log-sum-exp, draw keys)
+  add(W_SAMP_ROW, (size_t)d->vocab * 4);   // fp32 logits of a prompt's last row (sampled prefill)
+  {   // K-part partial sums of the split GEMMs: residual (O, down), gate/up and the other projections
     const int kt = d->dtype == DFLOW_BF16 ? TT<bf16>::KT : TT<float>::KT;
     const int nc = d->n_draft_layers * 2 * kvd;
     const int rs_epi[8] = {EPI_RESID, EPI_RESID, EPI_SWIGLU, EPI_STORE_F32, EPI_STORE_F32, EPI_STORE_T, EPI_BIAS_SILU,
@@ -227,24 +226,24 @@ Layout plan(const dflow_dims* d, int* nsplit_out, int* lm_groups_out) {
       const size_t r = (size_t)split_parts(rs_epi[i], rs_n[i] / 16, rs_k[i] / kt) * rows * rs_n[i] * 4;
       if (r > need) need = r;
     }
-    add(need);
+    add(W_KPART, need);
   }
-  {   // 27..32 matrix-core-order operand copies
+  {   // matrix-core-order operand copies
     const size_t fr = (size_t)((mmax + 15) / 16 * 16) * elt;
     const size_t round_fr = (size_t)((rows_round + 15) / 16 * 16) * elt;
-    add(fr * d->d);                                       // 27 x
-    add(fr * qd);                                         // 28 attention output
-    add(fr * (d->ffn > d->relay_hidden ? d->ffn : d->relay_hidden));   // 29 SwiGLU / relay hidden
-    add(round_fr * d->n_capture * d->d);                  // 30 captured states of the round
-    add(round_fr * 3 * d->d);                             // 31 relay input
-    add(round_fr * d->d);                                 // 32 projected features of the round
+    add(W_XF, fr * d->d);
+    add(W_ATTNF, fr * qd);   // attention output
+    add(W_ACTF, fr * (d->ffn > d->relay_hidden ? d->ffn : d->relay_hidden));   // SwiGLU / relay hidden
+    add(W_HCAPF, round_fr * d->n_capture * d->d);   // captured states of the round
+    add(W_UF, round_fr * 3 * d->d);   // relay input
+    add(W_FF, round_fr * d->d);   // projected features of the round
   }
-  add((size_t)mmax * 4);                                  // 33 rs: RMSNorm row scales
-  add(MAX_ROWS / 64 * 4);                                 // 34 arrival counters of the residual GEMMs (zero between launches)
-  {   // 35, 36 captured states and features of a prefill chunk
+  add(W_RS, (size_t)mmax * 4);   // RMSNorm row scales
+  add(W_ARRIVE, MAX_ROWS / 64 * 4);   // arrival counters of the residual GEMMs (zero between launches)
+  {   // captured states and features of a prefill chunk
     const size_t pre_fr = (size_t)((d->max_rows + 15) / 16 * 16) * elt;
-    add(pre_fr * d->n_capture * d->d);
-    add(pre_fr * d->d);
+    add(W_PRE_HCAPF, pre_fr * d->n_capture * d->d);
+    add(W_PRE_FF, pre_fr * d->d);
   }
   L.total = o;
   if (nsplit_out) *nsplit_out = nsplit;
@@ -322,38 +321,38 @@ extern "C" int dflow_create(const dflow_dims* dims, const dflow_weights* w, cons
   c->ws = workspace;
   c->ws_bytes = L.total;
   char* b = (char*)c->ws;
-  c->x = b + L.off[0];
-  c->qkv = b + L.off[2];
-  c->q = b + L.off[3];
-  c->hcap = b + L.off[6];
-  c->f = b + L.off[7];
-  c->fproj = (float*)(b + L.off[9]);
-  c->bg = (float*)(b + L.off[10]);
-  c->part_o = (float*)(b + L.off[11]);
-  c->part_ml = (float*)(b + L.off[12]);
-  c->rope = (float2*)(b + L.off[13]);
-  c->amax = (uint64_t*)(b + L.off[14]);
-  c->carry_rec = (int*)(b + L.off[15]);
+  c->x = b + L.off[W_X];
+  c->qkv = b + L.off[W_QKV];
+  c->q = b + L.off[W_Q];
+  c->hcap = b + L.off[W_HCAP];
+  c->f = b + L.off[W_F];
+  c->fproj = (float*)(b + L.off[W_FPROJ]);
+  c->bg = (float*)(b + L.off[W_BG]);
+  c->part_o = (float*)(b + L.off[W_PART_O]);
+  c->part_ml = (float*)(b + L.off[W_PART_ML]);
+  c->rope = (float2*)(b + L.off[W_ROPE]);
+  c->amax = (uint64_t*)(b + L.off[W_AMAX]);
+  c->carry_rec = (int*)(b + L.off[W_CARRY]);
   c->status = status;
-  c->tmp_pos = (int*)(b + L.off[17]);
-  c->ssq = (float*)(b + L.off[19]);
-  c->amax_part = (uint64_t*)(b + L.off[20]);
-  c->counters = (unsigned*)(b + L.off[21]);
-  c->ctxkv = b + L.off[22];
-  c->dknorm = (const void**)(b + L.off[23]);
-  c->samp = b + L.off[24];
-  c->samp_row = (float*)(b + L.off[25]);
-  c->kpart = (float*)(b + L.off[26]);
-  c->xf = b + L.off[27];
-  c->attnf = b + L.off[28];
-  c->actf = b + L.off[29];
-  c->hcapf = b + L.off[30];
-  c->uf = b + L.off[31];
-  c->ff = b + L.off[32];
-  c->rs = (float*)(b + L.off[33]);
-  c->arrive = (unsigned*)(b + L.off[34]);
-  c->pre_hcapf = b + L.off[35];
-  c->pre_ff = b + L.off[36];
+  c->tmp_pos = (int*)(b + L.off[W_TMP_POS]);
+  c->ssq = (float*)(b + L.off[W_SSQ]);
+  c->amax_part = (uint64_t*)(b + L.off[W_AMAX_PART]);
+  c->counters = (unsigned*)(b + L.off[W_COUNTERS]);
+  c->ctxkv = b + L.off[W_CTXKV];
+  c->dknorm = (const void**)(b + L.off[W_DKNORM]);
+  c->samp = b + L.off[W_SAMP];
+  c->samp_row = (float*)(b + L.off[W_SAMP_ROW]);
+  c->kpart = (float*)(b + L.off[W_KPART]);
+  c->xf = b + L.off[W_XF];
+  c->attnf = b + L.off[W_ATTNF];
+  c->actf = b + L.off[W_ACTF];
+  c->hcapf = b + L.off[W_HCAPF];
+  c->uf = b + L.off[W_UF];
+  c->ff = b + L.off[W_FF];
+  c->rs = (float*)(b + L.off[W_RS]);
+  c->arrive = (unsigned*)(b + L.off[W_ARRIVE]);
+  c->pre_hcapf = b + L.off[W_PRE_HCAPF];
+  c->pre_ff = b + L.off[W_PRE_FF];
 
   // RoPE table: angle p * theta^(-2i/Dh) evaluated in double
   const int half = dims->head_dim / 2;

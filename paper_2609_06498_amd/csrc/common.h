@@ -109,7 +109,6 @@ __device__ inline void frag_st(const FragOut& f, int m, int c, float v) {
   if (f.p) TT<T>::st(reinterpret_cast<T*>(f.p), afrag_off<T>(m, f.c0 + c, f.ktiles), v);
 }
 
-// 16 consecutive elements (16-byte aligned) <-> fp32, stores rounded to the storage type
 // n consecutive values of row m from column c (c and n multiples of KL, the
 // producer's c0 too) as whole 16-byte lane fragments of the copy
 template <typename T>
@@ -157,6 +156,7 @@ template <> struct Run4<bf16> {
   }
 };
 
+// 16 consecutive elements (16-byte aligned) <-> fp32, stores rounded to the storage type
 template <typename T> struct Row16;
 template <> struct Row16<bf16> {
   __device__ static inline void load(const bf16* p, float* v) {
