@@ -373,20 +373,25 @@ typedef TileShape<2, 2, 4, 2, 3> Tile128x64;
 typedef TileShape<1, 4, 4, 2, 3> Tile64x128;
 typedef TileShape<2, 2, 2, 2, 4> Tile64x64;
 typedef TileShape<4, 2, 4, 4, 1> Tile256x128;
+// fp32 is bound by the matrix cores (four ops of a quarter of the work per k
+// tile), so no tile size saves time and the smallest fills the chip best: 64 x
+// 64 takes 0.27 us a k tile alone and 0.24 in turn, where 128 x 128, four times the
+// work, takes 0.96 to 1.1 (0.93 to 1.0 in turn).  It was the fastest of the four or
+// within 1 % at 56 to 1024 rows of 512 to 32768 columns (400 x 32000 x 512: 112 us,
+// 130 at 128 x 128), so fp32 has no other.
 struct TileCost { int bm, bs; double t1, tn; };
 constexpr TileCost TILES[] = {{128, 8, 0.26, 0.28}, {128, 4, 0.18, 0.165}, {64, 8, 0.19, 0.165}, {64, 4, 0.15, 0.115},
                               {256, 8, 0.38, 0.48}};
 constexpr int N_TILES = sizeof(TILES) / sizeof(TILES[0]);
-// fp32 is bound by the matrix cores, not by LDS reads: no widest tile
-template <typename T> constexpr int tiles_of() { return sizeof(T) == 2 ? N_TILES : N_TILES - 1; }
+constexpr TileCost TILE_F32 = {64, 4, 0.27, 0.24};
 
 // the fastest tile for M rows x ntiles strips x ktiles in ks K parts, and its time in us
 template <typename T>
 static int pick_tile(int M, int ntiles, int ktiles, int ks, int cus, double* us) {
   int best = 0;
   double tb = 1e30;
-  for (int i = 0; i < tiles_of<T>(); ++i) {
-    const TileCost& c = TILES[i];
+  for (int i = 0; i < (sizeof(T) == 2 ? N_TILES : 1); ++i) {
+    const TileCost& c = sizeof(T) == 2 ? TILES[i] : TILE_F32;
     const long long wgs = (long long)((M + c.bm - 1) / c.bm) * ((ntiles + c.bs - 1) / c.bs) * ks;
     const long long n = (wgs + cus - 1) / cus;
     const double t = (double)n * ((ktiles + ks - 1) / ks) * (n == 1 ? c.t1 : c.tn);
@@ -419,13 +424,13 @@ static hipError_t launch_tile(const GemmParams& p, int waves, int ks, hipStream_
   if (!p.Af || (p.norm && !p.rs)) return hipErrorInvalidValue;
   double us;
   const int tile = pick_tile<T>(p.M, p.ntiles, p.ktiles, ks, p.cus > 0 ? p.cus : 256, &us);
-  if constexpr (tiles_of<T>() > 4)
-    if (tile == 4) return launch_tile_shape<T, EPI, Tile256x128>(p, waves, ks, st);
-  switch (tile) {
-    case 0: return launch_tile_shape<T, EPI, Tile128x128>(p, waves, ks, st);
-    case 1: return launch_tile_shape<T, EPI, Tile128x64>(p, waves, ks, st);
-    case 2: return launch_tile_shape<T, EPI, Tile64x128>(p, waves, ks, st);
-  }
+  if constexpr (sizeof(T) == 2)
+    switch (tile) {
+      case 0: return launch_tile_shape<T, EPI, Tile128x128>(p, waves, ks, st);
+      case 1: return launch_tile_shape<T, EPI, Tile128x64>(p, waves, ks, st);
+      case 2: return launch_tile_shape<T, EPI, Tile64x128>(p, waves, ks, st);
+      case 4: return launch_tile_shape<T, EPI, Tile256x128>(p, waves, ks, st);
+    }
   return launch_tile_shape<T, EPI, Tile64x64>(p, waves, ks, st);
 }
 
