@@ -360,7 +360,10 @@ __global__ void __launch_bounds__(512) gemm_kernel(GemmParams p) {
 // fall on the compute units.  Measured on the Qwen3 projections (8 x 64 .. 64 x
 // 200 k tiles per workgroup, bf16): a workgroup's k tile takes t1 us when it has
 // its compute unit to itself and tn when the unit holds several, one after
-// another where the tile leaves no room for a second.
+// another where the tile leaves no room for a second.  (Weights that come from
+// HBM for the first time take longer alone: 64 x 64 0.16 to 0.20 us, 128 x 64 0.21
+// to 0.23, 128 x 128 0.26 to 0.30.  The table only ranks launches, and those
+// figures rank them worse.)
 // LDS reads bound full launches: a wave of 64 x 32 reads 6 KB per 8 matrix ops,
 // one of 64 x 64 8 KB per 16, so the widest tile takes 0.48 us a k tile for twice the
 // work of the 128 x 128 one's 0.28 (8B LM head at 512 rows 695 -> 617 us, gate/up
@@ -639,8 +642,14 @@ __global__ void __launch_bounds__(256) range_reduce_kernel(GemmParams p, const f
 // compute units idle, one per range (fp32 partial sums to part_ws, folded by a
 // reduce kernel), whichever is estimated faster.  A reduce takes about 4 us
 // plus its bytes at 6.5 TB/s (measured: four parts of 128 x 4096 5 us, of 1024
-// x 4096 14.7 us), and so do the partial sums' writes; the row scales of a
-// whole residual launch add about 3 us.
+// x 4096 14.7 us), and so do the partial sums' writes.  The epilogue of a whole
+// residual launch takes 4 us more than a plain store at small outputs and 8 to 22
+// at 2 to 5 million (4 us + 3.5 per million); its parts were fitted with it: 6 us
+// and 5 TB/s.  On 285 residual launches (56 .. 1024 rows of the Qwen3, small
+// and tiny shapes' O and down, both ways measured) the choice is off by 42 us in
+// sum, by 9 at most (8B down, 868 rows: 114 us, 105 in parts); charging the
+// epilogue 3 us flat it was 217 and 36 (32B down, 640 rows: 219 us whole, 183 in
+// parts; 8B O, 512 rows: 40.6 and 35.9).
 template <typename T>
 static int tile_parts(int epi, const GemmParams& p) {
   const int nw = split_parts(epi, p.ntiles, p.ktiles);
@@ -649,9 +658,9 @@ static int tile_parts(int epi, const GemmParams& p) {
   double whole, split;
   pick_tile<T>(p.M, p.ntiles, p.ktiles, 1, cus, &whole);
   pick_tile<T>(p.M, p.ntiles, p.ktiles, nw, cus, &split);
-  const double part_us = (double)p.M * p.ntiles * 16 * 4 / 6.5e6;   // one part's sums, once over memory
-  const double fold1 = epi == EPI_RESID ? 3.0 : 0.0;
-  return split + 4.0 + 2.0 * nw * part_us < whole + fold1 ? nw : 1;
+  const double outputs = (double)p.M * p.ntiles * 16, moved = 2.0 * nw * outputs * 4;   // the sums: written and read
+  if (epi == EPI_RESID) return split + 6.0 + moved / 5.0e6 < whole + 4.0 + 3.5e-6 * outputs ? nw : 1;
+  return split + 4.0 + moved / 6.5e6 < whole ? nw : 1;
 }
 
 // fp32 partial sums of ks parts (each folding `waves` ranges) to part_ws
