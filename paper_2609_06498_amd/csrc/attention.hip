@@ -656,8 +656,9 @@ __global__ void __launch_bounds__(NW * 64) attn_kernel(AttnParams p) {
 // Workgroup: RB rows of one head, DH / CL lanes per row with CL channels each.
 template <typename T, int DH, int RB, int CL>
 __global__ void __launch_bounds__(RB * DH / CL) attn_combine_kernel(AttnParams p) {
-  const int row = blockIdx.x * RB + threadIdx.x / (DH / CL);   // s*Bq + j
-  if (row >= p.nseq * p.Bq) return;
+  // s*Bq + j (uniform with one row per workgroup: its positions and addresses stay scalar)
+  const int row = RB == 1 ? (int)blockIdx.x : blockIdx.x * RB + threadIdx.x / (DH / CL);
+  if (RB > 1 && row >= p.nseq * p.Bq) return;
   const int hq = blockIdx.y;
   const int d = threadIdx.x % (DH / CL) * CL;
   const int s = row / p.Bq, j = row - s * p.Bq;
@@ -665,8 +666,8 @@ __global__ void __launch_bounds__(RB * DH / CL) attn_combine_kernel(AttnParams p
   const int kvh = hq / G, g = hq - kvh * G;
   const int ar = j * G + g;
   const int rgi = ar >> 4, r = ar & 15;
-  const int kv_len = p.start_pos[s] + p.Bq;
-  int ns = p.row_splits ? (p.start_pos[s] + j) / p.split_keys + 1 : (kv_len + p.split_keys - 1) / p.split_keys;
+  const int keys = p.start_pos[s] + (p.row_splits ? j + 1 : p.Bq);
+  int ns = (keys + p.split_keys - 1) / p.split_keys;
   if (ns > p.nsplit) ns = p.nsplit;
   const size_t base = (((size_t)s * p.Hkv + kvh) * p.rg + rgi) * p.nsplit;
   const float* ml = p.part_ml + base * 32 + 2 * r;

@@ -34,6 +34,8 @@ struct AttnParams {
   int nseq, Bq, Hq, Hkv, Dh;
   int causal;                // 1: row j sees keys <= start+j; 0: all keys < start+Bq
   int split_keys;            // keys per split: `chunks` chunks of split_keys_for keys, at most 64 pages
+  // (among the fields that the combine reads first, so they arrive in one load)
+  int row_splits;            // 1: the combine merges the splits up to each row's own position (prefill)
   int chunks;                // chunks per split (resident in LDS one after another); 1 when the
                              // launch has more 16-row groups than attention_waves
   int nsplit;                // split slots per sequence for this launch (grid and partial stride)
@@ -41,7 +43,6 @@ struct AttnParams {
   int rg;                    // 16-row groups per (seq, kv head)
   float* part_o;             // [nseq][Hkv][rg][nsplit][16][Dh]
   float* part_ml;            // [nseq][Hkv][rg][nsplit][16][2]
-  int row_splits;            // 1: the combine merges the splits up to each row's own position (prefill)
   FragOut outf;              // [nseq*Bq, Hq*Dh] output in matrix-core order, the O projection's operand
   int out_row0;              // output row of row 0
   // pf_wgs extra workgroups (after the nseq*Hkv*nsplit attention ones) read
