@@ -11,7 +11,7 @@ namespace dflow {
 // ---------------------------------------------------------------- embedding
 // Also writes the per-16-column-strip sums of squares of the row (the
 // RMSNorm row scale of the next projection), ssq[row * ssq_ld + c], and that
-// scale itself.
+// scale itself (rs_out null: not needed).
 template <typename T>
 __global__ void embed_kernel(const int* tok, const T* E, int V, int d, T* out, int* status, float* ssq, int ssq_ld,
                              float* rs_out, float eps, FragOut of) {
@@ -34,6 +34,7 @@ __global__ void embed_kernel(const int* tok, const T* E, int V, int d, T* out, i
     ssq[(size_t)row * ssq_ld + c] = sq;
     s_sq[c] = sq;
   }
+  if (!rs_out) return;
   __syncthreads();
   row_scale_store(s_sq, d / 16, eps, rs_out + row);
 }
@@ -147,11 +148,11 @@ hipError_t launch_rmsnorm(bool isbf, bool in_f32, const void* x, int ldx, int M,
 // Workgroup: 2048 / DH consecutive rows of one head (head < nq is a query head,
 // then Hkv key heads, then Hkv value heads); DH / 8 lanes per row, each with four
 // channels of the lower half and their rotation partners in the upper half, so
-// a row's loads and stores are 16 and 8 bytes a lane and its sum of squares
-// takes one lane's eight terms and log2(DH / 8) exchanges.  Consecutive rows
+// a row's loads and stores are 16 and 8 bytes a lane (and its sum of squares
+// takes four exchanges a level).  Consecutive rows
 // together, because their keys and values share the cache lines of a page.
 // Bound by memory traffic, the two-byte value stores most of all (a lane's
-// channels lie 16 bytes apart in fragment order): 16.7 us for 1024 rows of the
+// channels lie 16 bytes apart in fragment order): 17.1 us for 1024 rows of the
 // Qwen3-8B shape, where one wave per (row, head) with 4-byte accesses took 20.8; 64
 // rows of the 32B shape 5.5 us.
 template <typename T, int DH>
@@ -418,7 +419,7 @@ hipError_t launch_relay_gather(bool isbf, int carry_on, const int* carry_rec, co
 }
 
 // x[s*B + 0] = E(anchor); relayed rows: E_mask + beta * LN(h) + gamma; others E_mask.
-// Also writes the per-16-column-strip sums of squares of the stored row and its RMSNorm scale.
+// Also writes the per-16-column-strip sums of squares of the stored row and its RMSNorm scale (rs_out null: not needed).
 // Thread t owns the 16-column chunks t, t + 256, ... (d <= 16 * 256 * RC);
 // the carried state is read once and kept in registers for both LayerNorm passes.
 template <typename T>
@@ -512,6 +513,7 @@ __global__ void __launch_bounds__(256) relay_input_kernel(int carry_on, const in
     ssq[(size_t)row * ssq_ld + c] = sq;
     s_sq[c] = sq;
   }
+  if (!rs_out) return;
   __syncthreads();
   row_scale_store(s_sq, nc, rms_eps, rs_out + row);
 }
