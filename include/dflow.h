@@ -213,11 +213,11 @@ int dflow_qkv_parts(const dflow_ctx* ctx);
 /* Attention work split of the round calls (verify and draft): *chunk_keys
  * receives the keys of one LDS-resident chunk (128 or 256) and *chunks the
  * chunks per split (a split covers chunks * chunk_keys keys at fixed absolute
- * positions, the running softmax carried across its chunks; a call
- * whose query rows need more row groups than one workgroup has waves uses one
- * chunk per split, and prefill has splits of its own).  Fixed at create from max_batch, the kv heads and the
- * capacity; for tests and byte accounting.  Returns 0, or DFLOW_EINVAL on a
- * null argument. */
+ * positions, the running softmax carried across its chunks; a call whose query
+ * rows need more row groups than one workgroup has waves uses one chunk per
+ * split, and prefill has splits of its own).  Fixed at create from max_batch,
+ * the kv heads and the capacity; for tests and byte accounting.  Returns 0, or
+ * DFLOW_EINVAL on a null argument. */
 int dflow_attention_split(const dflow_ctx* ctx, int* chunk_keys, int* chunks);
 
 /* Prompt processing for sequence slot `seq` (set-up, not part of the round):
@@ -229,9 +229,9 @@ int dflow_attention_split(const dflow_ctx* ctx, int* chunk_keys, int* chunks);
 int dflow_prefill(dflow_ctx* ctx, hipStream_t stream, int seq, const int32_t* tok, int len, int32_t* first_anchor);
 
 /* Prompt processing of nseq sequences in slots 0..nseq-1: the results of
- * dflow_prefill of each, computed in shared row chunks.  tok: device, the prompts back to back (sum of len tokens); len: HOST
- * [nseq] prompt lengths (the host plans the row chunks, so the lengths are
- * host values); first_anchor: device [nseq].  Every length is checked before
+ * dflow_prefill of each, computed in shared row chunks.  tok: device, the
+ * prompts back to back (sum of len tokens); len: HOST [nseq] prompt lengths (the
+ * host plans the row chunks, so the lengths are host values); first_anchor: device [nseq].  Every length is checked before
  * anything is launched. */
 int dflow_prefill_batch(dflow_ctx* ctx, hipStream_t stream, int nseq, const int32_t* tok, const int32_t* len,
                         int32_t* first_anchor);

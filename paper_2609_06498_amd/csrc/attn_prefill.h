@@ -17,12 +17,12 @@
 // Reference of a row's exponentials: with bf16 probabilities the page's own
 // maximum, so that the largest probability of every page is exactly 1 and free of
 // rounding.  The running maximum over a 2048-key split rounds all but one page's;
-// the keys and values after it were 0.2 to 0.5 % further from the 64-bit ones
-// than with 128-key splits, and are 0.1 to 0.2 % nearer than those now (8B and
-// 1.7B prompts).  It falls at most SPAN (log2 units) below the row's largest
+// the keys and values after it were 0.14 to 0.52 % further from the 64-bit ones
+// than with 128-key splits, and are 0.04 to 0.29 % nearer than those now (8B
+// and 1.7B prompts).  It falls at most SPAN (log2 units) below the row's largest
 // score so far, so the rescales stay below 2^SPAN times what a running maximum
-// keeps.  Cost: the rescale is hardly ever skipped, 0.1 to 0.4 % of a whole
-// prompt (1.7B shape, 12288 keys: 10074 -> 10113 us).  fp32 probabilities are
+// keeps.  Cost: the rescale is hardly ever skipped, 1.1 % of the attention, 0.1
+// to 0.4 % of a whole prompt (1.7B shape, 12288 tokens: 10074 -> 10113 us).  fp32 probabilities are
 // not rounded: SPAN 0, the running maximum.
 //
 // A split's result goes straight to the output when it is the row's only one,
@@ -34,8 +34,8 @@
 // groups), the vector unit (64 keys x 16 rows: 16 exponentials per lane and
 // their scale, maximum, sum and conversion, about 600 clocks) and the matrix
 // cores (32 ops of 16 clocks) are of one size.  Qwen3-1.7B shape, 512 rows
-// against 12288 keys: 73 us + 11 us combine, where 256-key splits of the round
-// kernel with their partials took 150 + 50.
+// against 11.8 thousand keys: 82 us (80 with the running maximum) + 8 us combine,
+// where 256-key splits of the round kernel with their partials took 150 + 50.
 #pragma once
 #include "common.h"
 #include "kernels.h"
