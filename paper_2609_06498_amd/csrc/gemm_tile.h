@@ -289,8 +289,10 @@ __global__ void __launch_bounds__(S::NW * 64, S::OCC * S::NW / 4) gemm_tile_kern
         }
         if (p.logits && row) {
           float* o = p.logits + (size_t)m * p.ldl + colbase + nt * 16 + 4 * q;
-          *reinterpret_cast<float4*>(o) = make_float4(v[0], v[1], v[2], v[3]);
-          if (pair) *reinterpret_cast<float4*>(o + 16) = make_float4(v[4], v[5], v[6], v[7]);
+          // (the caller's buffer: aligned as floats are, not to 16 bytes)
+          typedef float run_t __attribute__((ext_vector_type(4), aligned(4)));
+          *reinterpret_cast<run_t*>(o) = run_t{v[0], v[1], v[2], v[3]};
+          if (pair) *reinterpret_cast<run_t*>(o + 16) = run_t{v[4], v[5], v[6], v[7]};
         }
         const float first = __shfl(v[0], c16, 64);   // the group's first column (lane group 0)
         float best = -INFINITY;

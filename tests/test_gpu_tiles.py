@@ -131,3 +131,30 @@ def test_round_rows_bitwise(b):
     # the argmax of the logits themselves
     assert torch.equal(many[1][1].argmax(-1).int(), many[1][3])
     rt.close()
+
+
+def test_logits_at_any_float():
+    """The logits buffers are the caller's: one that starts between two 16-byte
+    boundaries takes the same values (64 rows, the tiles' vector stores)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_06498_amd import Runtime
+    from paper_2609_06498_amd.session import Session
+    dims, B, b = DIMS["bf16-narrow"], 16, 4
+    r = np.random.default_rng(17)
+    prompts = [r.integers(0, dims.vocab, size=n).astype(np.int32) for n in (5, 30, 17, 9)]
+    rt = Runtime(dims, B, b, 64, make_weights(dims, 11))
+    got = []
+    for off in (0, 1):
+        s = Session(rt, b)
+        s.prefill(prompts)
+        n = b * B * dims.vocab
+        lg, dl = (torch.full((n + 8,), -7.0, dtype=torch.float32, device="cuda") for _ in range(2))
+        s.round(True, draft_logits=dl[off:off + n], logits=lg[off:off + n])
+        assert rt.status() == 0
+        for x in (dl, lg):      # nothing outside
+            assert bool((x[:off] == -7).all()) and bool((x[off + n:] == -7).all())
+        got.append([dl[off:off + n].clone(), lg[off:off + n].clone(), s.tgt.clone(), s.block.clone()])
+    rt.close()
+    for i, (x, y) in enumerate(zip(*got)):
+        assert torch.equal(x, y), f"output {i} differs"
