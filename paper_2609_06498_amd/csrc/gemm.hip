@@ -68,8 +68,9 @@ __global__ void __launch_bounds__(512) gemm_kernel(GemmParams p) {
   const int ast = p.Af ? 64 : KT * (int)sizeof(T) / 16;
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
-    if (p.Af) {   // rows past M in the last row tile are read and never stored
-      arow[i] = (const gu4*)(p.Af) + (size_t)min(i, mtiles - 1) * p.ktiles * 64 + lane;
+    if (p.Af) {   // lanes of rows past M read the last row (never stored; few rows then touch few lines)
+      const int rt = min(i, mtiles - 1);
+      arow[i] = (const gu4*)(p.Af) + (size_t)rt * p.ktiles * 64 + (lane & 48) + min(lane & 15, M - 1 - rt * 16);
     } else {
       const int m = min(i * 16 + (lane & 15), M - 1);
       arow[i] = (const gu4*)(Ap + (size_t)m * p.lda + (lane >> 4) * KL);
